@@ -174,7 +174,7 @@ int resq_linear_fwd(int format, int sparsity, const uint16_t* X, int64_t m, int6
  * wprep     : output, device buffer of resq_prepared_weights_size(format, n, d) bytes,
  *             256-byte aligned.  The contents are an internal layout (the MFMA operand
  *             encoding of the same values: for MXFP4 the same E2M1/E8M0 codes, for HiF4 each
- *             element k 2^-b as a BF6 E3M2 code next to the block's level-1 scale code).
+ *             element k 2^-b as an FP6 E2M3 code next to the block's level-1 scale code).
  * resq_linear_fwd_prepared is resq_linear_fwd with Q(W) given in this form; results are
  * identical.  Its workspace size is resq_workspace_size(RESQ_OP_LINEAR_FWD_PREPARED, ...).
  */

@@ -189,47 +189,56 @@ __device__ __forceinline__ uint32_t even_bits16(uint32_t x) {
 }
 
 // ------------------------------------------------------------------------------------------
-// MFMA operand encodings for HiF4 (f8f6f4 MFMA, formats: 2 = FP6 E2M3, 3 = BF6 E3M2)
+// MFMA operand encodings for HiF4 (f8f6f4 MFMA, formats: 2 = FP6 E2M3, 4 = FP4 E2M1)
 // ------------------------------------------------------------------------------------------
-// Activation side: V = k (4+m) 2^(2-b) <= 196 (value = V 2^(e-37)) is split V = 16 hi + lo;
-// hi, lo <= 15 are E2M3 codes of hi/8, lo/8 (E2M3 code t has value t/8 for t <= 15), each
-// with the element's sign in bit 5.  Scales: hi term 2^(e-30) -> E8M0 e + 97, lo term
-// 2^(e-34) -> E8M0 e + 93.
-// hif4_split4 splits the four elements of one level-3 group (shift b) at once: their codes in
-// the low nibbles of the bytes of nb (high nibbles ignored), q2 = 4+m in both 16-bit lanes.
-// One 16-bit-lane multiply forms the four products k (4+m) <= 49 (no carry crosses a byte)
-// and one shift applies 2 - b (V <= 196 stays in its byte); the four 6-bit hi and lo fields
-// then close up into 24 bits each, field j at bit 6j.
-__device__ __forceinline__ uint32_t close_up6x4(uint32_t x) {  // bytes f0..f3 (< 64) -> 24 bits
+// Close four 6-bit fields, one per byte, up into 24 bits, field j at bit 6j.
+__device__ __forceinline__ uint32_t close_up6x4(uint32_t x) {
   const uint32_t t = (x & 0x003F003Fu) | ((x >> 2) & 0x0FC00FC0u);
   return (t & 0xFFFu) | ((t >> 4) & 0xFFF000u);
 }
-__device__ __forceinline__ void hif4_split4(uint32_t nb, uint32_t q2, uint32_t b, uint32_t& hi24, uint32_t& lo24) {
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  const uint32_t k = nb & 0x07070707u, sg = (nb & 0x08080808u) << 2;
-  const uint32_t kq = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, k) * __builtin_bit_cast(u16x2, q2));
-  const uint32_t V = kq << (2u - b);
-  hi24 = close_up6x4(sg | ((V >> 4) & 0x0F0F0F0Fu));
-  lo24 = close_up6x4(sg | (V & 0x0F0F0F0Fu));
+
+// Activation side: V = k (4+m) 2^(2-b) <= 196 (value = V 2^(e-37)) has at most six significant
+// bits, so V = 32 hi + 2 lo with hi the largest E2M3 value not above V / 32 and lo an exact E2M1
+// value (the remainder is 0..3 units of a quarter or less of hi's step).  Both carry the
+// element's sign.  Scales: hi 2^(e-32), stored as E8M0 e + 95; lo 2^(e-36), the same byte with
+// the weight operand scaled by 2^-4.
+// The codes of k = 0..7 come from a byte table per (m, b), entry 3m + b: x, y the E2M3 codes of
+// k = 0..3, 4..7, z, w the E2M1 codes.  A kernel keeps a copy in LDS (hif4_load_split_tab).
+constexpr int kHiSplitEntries = 12;
+static __device__ const uint4 kHiSplitTab[kHiSplitEntries] = {
+    {0x0C080400u, 0x16141210u, 0x00000000u, 0x00000000u}, {0x06040200u, 0x0E0C0A08u, 0x00000000u, 0x00000000u},
+    {0x03020100u, 0x07060504u, 0x00000000u, 0x00000000u},
+    {0x0F0A0500u, 0x18171412u, 0x00000000u, 0x07000400u}, {0x07050200u, 0x100F0C0Au, 0x02000200u, 0x05000200u},
+    {0x03020100u, 0x08070605u, 0x03020100u, 0x03020100u},
+    {0x110C0600u, 0x1A191714u, 0x00000000u, 0x06000000u}, {0x09060300u, 0x12110F0Cu, 0x00000000u, 0x04000000u},
+    {0x04030100u, 0x0A090706u, 0x02000200u, 0x02000200u},
+    {0x120E0700u, 0x1C1A1816u, 0x04000000u, 0x04060700u}, {0x0A070300u, 0x1412100Eu, 0x02000200u, 0x02040500u},
+    {0x05030100u, 0x0C0A0807u, 0x01020300u, 0x01020300u}};
+
+// Threads 0 .. 11 of the workgroup fill the LDS copy; the caller's next barrier publishes it.
+__device__ __forceinline__ void hif4_load_split_tab(uint4* lds) {
+  if (threadIdx.x < kHiSplitEntries) lds[threadIdx.x] = kHiSplitTab[threadIdx.x];
+}
+__device__ __forceinline__ uint32_t hif4_act_scale(uint32_t c1) { return (c1 >> 2) + 95u; }
+
+// The four elements of one level-3 group, their codes in the low nibbles of the bytes of nb
+// (high nibbles ignored), t the table entry of (m, b): four 6-bit hi fields in 24 bits, four
+// 4-bit lo fields in 16 bits.
+__device__ __forceinline__ void hif4_split4(uint32_t nb, const uint4& t, uint32_t& hi24, uint32_t& lo16) {
+  const uint32_t k = nb & 0x07070707u, sg = nb & 0x08080808u;
+  hi24 = close_up6x4(__builtin_amdgcn_perm(t.y, t.x, k) | (sg << 2));
+  const uint32_t l = __builtin_amdgcn_perm(t.w, t.z, k) | sg;
+  lo16 = __builtin_amdgcn_perm(0u, l | (l >> 4), 0x0C0C0200u);
 }
 
-// Weight side: k 2^-b as a BF6 E3M2 code (value exact), sign in bit 5; the remaining
-// factor (4+m) 2^(e-35) is the E8M0 scale e + 92 times the per-column factor (4+m).  The
-// E3M2 code (bias 3) of k = 0..7 is 0, 12 (1.0), 16 (2.0), 18 (3.0), 20, 21, 22, 23, and the
-// shift b lowers the exponent field of a nonzero one by b.
-// hif4_e3m2x4 encodes the four elements of one level-3 group (shift b) at once, their codes
-// in the low nibbles of the bytes of nb (high nibbles ignored): the codes of k come from a
-// byte table by v_perm, nonzero ones lowered by b << 2 (at least 12 - 8, so no borrow crosses
-// a byte), the sign goes to bit 5, and the four 6-bit fields close up into 24 bits, field j
-// at bit 6j.
-__device__ __forceinline__ uint32_t hif4_e3m2x4(uint32_t nb, uint32_t b) {
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  const uint32_t k = nb & 0x07070707u;
-  const uint32_t e = __builtin_amdgcn_perm(0x17161514u, 0x12100C00u, k);  // 0 12 16 18 20 21 22 23
-  const uint32_t nz = ((k + 0x7F7F7F7Fu) & 0x80808080u) >> 7;              // 1 in each nonzero byte
-  const uint32_t sub = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, nz) *
-                                                        __builtin_bit_cast(u16x2, (4u * b) * 0x00010001u));
-  return close_up6x4(((nb & 0x08080808u) << 2) | (e - sub));
+// Weight side: k 2^-b as an E2M3 code (exact: 0..1.75 in steps of 1/4, ..., 7), sign in bit 5;
+// the level-1 scale (4+m) 2^(e-35) is applied to the accumulators per column.  The codes of
+// k = 0..7 come from a byte table by v_perm; the four elements of one level-3 group (shift b)
+// at once, their codes in the low nibbles of the bytes of nb, as 24 bits.
+__device__ __forceinline__ uint32_t hif4_e2m3x4(uint32_t nb, uint32_t b) {
+  const uint32_t lo = b == 0u ? 0x14100800u : b == 1u ? 0x0C080400u : 0x06040200u;
+  const uint32_t hi = b == 0u ? 0x1E1C1A18u : b == 1u ? 0x16141210u : 0x0E0C0A08u;
+  return close_up6x4(__builtin_amdgcn_perm(hi, lo, nb & 0x07070707u) | ((nb & 0x08080808u) << 2));
 }
 
 }  // namespace resq

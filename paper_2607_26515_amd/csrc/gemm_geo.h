@@ -1,4 +1,4 @@
-// Compile-time geometry of the FP4 GEMM (gemm.hip): the LDS image of one K step, the
+// Compile-time geometry of the MXFP4 GEMM (gemm.hip): the LDS image of one K step, the
 // assignment of copy instructions to waves, and each copy's source offset and LDS target.
 //
 // Plain C++17 with constexpr functions only (no HIP types or intrinsics), so that the kernel
@@ -16,25 +16,23 @@ namespace resq {
 constexpr uint32_t kBad = 0xFFFFFFF0u;  // an offset past every operand: the load returns 0
 constexpr int kDumpBytes = 1024;         // LDS target of the padding copies (never read)
 
-// Compile-time geometry of one configuration: FMT 0 MXFP4 / 1 HiF4; WM x WN waves per K group,
-// each owning TM x TN 32x32 output tiles; NT activation terms; NS LDS stages; KG K groups.
+// Compile-time geometry of one configuration: FMT 0 MXFP4 (HiF4 has its own geometry,
+// gemm_hif4_geo.h); WM x WN waves per K group, each owning TM x TN 32x32 output tiles; NT activation terms; NS LDS stages; KG K groups.
 template <int FMT, int WM, int WN, int TM, int TN, int NT, int NS, int KG>
 struct Geo {
+  static_assert(FMT == 0, "MXFP4");
   static constexpr int kFmt = FMT, kWM = WM, kWN = WN, kTM = TM, kTN = TN, kNT = NT, kNS = NS, kKG = KG;
   static constexpr int WT = WM * WN;                  // waves per K group
   static constexpr int W = WT * KG;                   // waves
   static constexpr int kThreads = 64 * W;
   static constexpr int MTW = WM * TM, NTW = WN * TN;  // row / column tiles per workgroup
-  static constexpr int FA = FMT == 0 ? 16 : 48;       // A lane record bytes (global)
-  static constexpr int FB = FMT == 0 ? 16 : 24;       // B lane record bytes (global)
+  static constexpr int FA = 16, FB = 16;              // lane record bytes (global)
   static constexpr int PA = FA / 16;                  // A: 16-byte planes per fragment
   static constexpr int A_FRAG = 64 * FA, B_FRAG = 64 * FB;  // bytes per fragment (global)
-  // LDS bytes per B fragment: a 12-byte copy lands each lane at a 16-byte stride
-  static constexpr int B_LDS = FMT == 0 ? 1024 : 2048;
+  static constexpr int B_LDS = 1024;                  // LDS bytes per B fragment
   static constexpr int SAJ = (MTW + 3) / 4;           // scale copies per A term (4 fragments each)
   static constexpr int SBJ = (NTW + 3) / 4;
-  // LDS image of one K step: A [term][row tile][plane][64 x 16 B]; B [col tile] one 16-byte
-  // plane (MXFP4) or two planes of 12 bytes per lane at a 16-byte stride (HiF4); A scales
+  // LDS image of one K step: A [term][row tile][64 x 16 B]; B [col tile][64 x 16 B]; A scales
   // [term][copy][4 x 64 B]; B scales [copy][4 x 64 B].  A stage holds KG such images (BLK
   // bytes apart), then the padding copies' dump area.
   static constexpr int B_OFF = NT * MTW * A_FRAG;
@@ -43,35 +41,31 @@ struct Geo {
   static constexpr int BLK = (SB_OFF + SBJ * 256 + 255) / 256 * 256;
   static constexpr int DUMP_OFF = KG * BLK;  // padding copies
   static constexpr int STAGE = DUMP_OFF + kDumpBytes;
-  // copy instructions per K step by class: A fragments (16 B per lane), B fragments (16 B
-  // per lane for MXFP4; two 12-byte halves for HiF4), scale bytes of A and B (4 B per lane);
-  // per stage KG times that; per wave: the class count rounded up to a multiple of W
-  static constexpr int JA1 = NT * MTW * PA, JB1 = FMT == 0 ? NTW : 2 * NTW, JS1 = NT * SAJ + SBJ;
+  // copy instructions per K step by class: A fragments and B fragments (16 B per lane), scale
+  // bytes of A and B (4 B per lane); per stage KG times that; per wave: the class count
+  // rounded up to a multiple of W
+  static constexpr int JA1 = NT * MTW * PA, JB1 = NTW, JS1 = NT * SAJ + SBJ;
   static constexpr int JA = KG * JA1, JB = KG * JB1, JS = KG * JS1;
   static constexpr int XA = (JA + W - 1) / W, XB = (JB + W - 1) / W, XS = (JS + W - 1) / W;
   static constexpr int JW = XA + XB + XS;
-  static constexpr int SZB = FMT == 0 ? 16 : 12;
+  static constexpr int SZB = 16;                      // bytes per lane of a B copy
   // the K groups' accumulators are summed through the (then idle) LDS of the stages
   static constexpr int RED = (KG - 1) * WT * TM * TN * 16 * 64 * 4;
   static constexpr size_t LDS = (size_t)(NS * STAGE > RED ? NS * STAGE : RED);
-  static size_t lds_bytes() { return LDS; }
   static_assert(NS >= 2, "at least two stages");
 };
 
-// Every configuration the GEMM instantiates, as X(format, tile configuration, WM, WN, TM, TN,
+// Every configuration of the MXFP4 GEMM, as X(format, tile configuration, WM, WN, TM, TN,
 // NS, KG); the tile configurations are 0: 64 x 64, 1: 128 x 256, 2: 128 x 192, 3: 128 x 192
 // in eight waves, 4: 64 x 128 (the numbering of resq_gemm_plan).  Each runs with one or two activation
 // terms.  launch_gemm dispatches from this list, and the protocol check walks it.
 #define RESQ_GEMM_CONFIGS(X)                                                                     \
   X(0, 0, 2, 2, 1, 1, 4, 2) X(0, 0, 2, 2, 1, 1, 4, 4) X(0, 0, 2, 2, 1, 1, 2, 4)                \
-  X(0, 0, 2, 2, 1, 1, 4, 1) X(0, 1, 2, 2, 2, 4, 4, 1)                \
-  X(1, 0, 2, 2, 1, 1, 4, 2) X(1, 0, 2, 2, 1, 1, 2, 2) X(1, 0, 2, 2, 1, 1, 2, 1)                \
-  X(1, 3, 4, 2, 1, 3, 2, 1) X(1, 2, 2, 2, 2, 3, 2, 1) X(0, 4, 2, 2, 1, 2, 4, 1)                \
-  X(1, 4, 2, 2, 1, 2, 2, 2)
+  X(0, 0, 2, 2, 1, 1, 4, 1) X(0, 1, 2, 2, 2, 4, 4, 1) X(0, 4, 2, 2, 1, 2, 4, 1)
 
-// HiF4 with more than one tile per wave keeps one register set and runs two waves per SIMD.
+// Every configuration keeps two register sets (step k+1's operands are read during step k).
 template <int FMT, int TM, int TN>
-constexpr bool kSingleSet = FMT == 1 && TM * TN > 1;
+constexpr bool kSingleSet = false;
 
 // One copy instruction of a wave: this lane's source offset at K step 0 (kBad: no source,
 // the lane copies zeros) and the stage-relative LDS destination (the dump area for copies
@@ -111,16 +105,16 @@ constexpr Slot slot_a(int wave, int x, int lane, const SlotArgs& a) {
   return c;
 }
 
-// Copy x of class B (fragments of operand B): column tile j, and for HiF4 the 12-byte half q.
+// Copy x of class B (fragments of operand B): column tile j.
 template <class G>
 constexpr Slot slot_b(int wave, int x, int lane, const SlotArgs& a) {
   const int jc = wave + G::W * x;
   Slot c{kBad, (uint32_t)G::DUMP_OFF, 0u};
   if (jc < G::JB) {
     const int kk = jc / G::JB1, jl = jc % G::JB1;
-    const int j = G::kFmt == 0 ? jl : jl / 2, q = G::kFmt == 0 ? 0 : jl % 2;
-    c.voff = a.N0 + j < a.nt ? a.b_frag_off + ((a.N0 + j) * a.nkb + kk) * G::B_FRAG + lane * G::FB + q * 12 : kBad;
-    c.lds = (uint32_t)(kk * G::BLK + G::B_OFF + j * G::B_LDS + q * 1024);
+    const int j = jl;
+    c.voff = a.N0 + j < a.nt ? a.b_frag_off + ((a.N0 + j) * a.nkb + kk) * G::B_FRAG + lane * G::FB : kBad;
+    c.lds = (uint32_t)(kk * G::BLK + G::B_OFF + j * G::B_LDS);
     c.kk = (uint32_t)kk;
   }
   return c;

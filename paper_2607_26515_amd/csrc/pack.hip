@@ -7,9 +7,10 @@
 // MXFP4 half step are zero codes.
 //
 //   MXFP4 (A or B): 16 B per lane (E2M1 nibbles) + 1 B per lane (E8M0 scale).
-//   HiF4 A (activations): 48 B per lane = E2M3 "hi" then "lo" (V = 16 hi + lo, see
-//                         device_fp4.h) + 1 B per lane (the level-1 code c1).
-//   HiF4 B (weights):     24 B per lane = BF6 E3M2 of k 2^-b + 1 B per lane (c1).
+//   HiF4 A (activations): 40 B per lane = 24 B E2M3 "hi", 16 B E2M1 "lo" (V = 32 hi + 2 lo,
+//                         see device_fp4.h) + 1 B per lane (hi's E8M0 scale).
+//   HiF4 B (weights):     24 B per lane = E2M3 of k 2^-b + 1 B per lane (level-1 code c1).
+//   (HiF4 fragments are stored as planes of 16- and 8-byte lane pieces, gemm_hif4_geo.h.)
 #include "kernels.h"
 #include "frag.h"
 
@@ -25,7 +26,7 @@ template <int MODE, int MASK>
 __device__ __forceinline__ void pack_record(const uint8_t* __restrict__ codes, const void* __restrict__ scales,
                                             int64_t rows, int64_t K, int64_t nkb, const uint8_t* __restrict__ gbits,
                                             uint8_t* __restrict__ frag, uint8_t* __restrict__ fscale, int64_t t,
-                                            int64_t kb, int l) {
+                                            int64_t kb, int l, const uint4* tab) {
   const int64_t gid = (t * nkb + kb) * 64 + l;
   const int64_t row = t * 32 + (l & 31);
   const int half = l >> 5;
@@ -48,7 +49,7 @@ __device__ __forceinline__ void pack_record(const uint8_t* __restrict__ codes, c
       if (!((gbits[bit >> 3] >> (bit & 7)) & 1u)) cw = make_uint4(0, 0, 0, 0);
     }
   }
-  store_frag_record<MODE>(frag, fscale, gid, cw, sc, half);
+  store_frag_record<MODE>(frag, fscale, gid, cw, sc, half, tab);
 }
 
 // grid: x covers the lane records of one row tile (64 per K step), y = row tiles (grid-stride)
@@ -59,11 +60,16 @@ __global__ __launch_bounds__(kThreads) void pack_kernel(const uint8_t* __restric
                                                         const uint8_t* __restrict__ gbits,
                                                         uint8_t* __restrict__ frag,
                                                         uint8_t* __restrict__ fscale) {
+  __shared__ uint4 tab[MODE == kPackHiA ? kHiSplitEntries : 1];
+  if constexpr (MODE == kPackHiA) {
+    hif4_load_split_tab(tab);
+    __syncthreads();
+  }
   const int64_t nkb = (K + 63) / 64;
   const int64_t local = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // kb * 64 + lane
   if (local >= nkb * 64) return;
   for (int64_t t = blockIdx.y; t < nfrag_rows; t += gridDim.y)
-    pack_record<MODE, MASK>(codes, scales, rows, K, nkb, gbits, frag, fscale, t, local >> 6, (int)(local & 63));
+    pack_record<MODE, MASK>(codes, scales, rows, K, nkb, gbits, frag, fscale, t, local >> 6, (int)(local & 63), tab);
 }
 
 // Zero fill of n floats (grid-stride).
@@ -82,7 +88,7 @@ void launch_zero_f32(float* p, int64_t n, hipStream_t s) {
 
 size_t frag_bytes(int mode, int64_t rows, int64_t K) {
   const int64_t n = ((rows + 31) / 32) * ((K + 63) / 64) * 64;
-  const int64_t per = mode == kPackMx ? 16 : (mode == kPackHiA ? 48 : 24);
+  const int64_t per = mode == kPackMx ? 16 : (mode == kPackHiA ? kHiAFrag / 64 : kHiBFrag / 64);
   return (size_t)(n * per);
 }
 

@@ -3,6 +3,7 @@
 #include "kernels.h"
 #include "profiler.h"
 #include "quant_core.h"
+#include "gemm_hif4_geo.h"
 #include "hist.h"
 
 namespace resq {
@@ -179,8 +180,8 @@ __global__ __launch_bounds__(kThreads) void residual_kernel(
 // tile, half (i/4)%2 and the 8-element slice i%4.  An MXFP4 scale block (32 elements) is 4
 // consecutive lanes, a HiF4 64-block 8 consecutive lanes, a HiF4 level-2 group one lane.
 // Each thread quantizes its slice, forms dX = X - Q(X) (exact in float32), quantizes dX,
-// applies S_k:4 or S_k:8 (whole groups inside the slice), and the 4 threads of a record write it as one contiguous 16-byte (MXFP4) or
-// 48-byte (HiF4 E2M3 hi | lo) run.  Rows past m, and the missing half of an MXFP4 K step
+// applies S_k:4 or S_k:8 (whole groups inside the slice), and the 4 threads of a record write it
+// (MXFP4: 16 contiguous bytes; HiF4: pieces of the fragment's planes, gemm_hif4_geo.h).  Rows past m, and the missing half of an MXFP4 K step
 // when d % 64 == 32, quantize zeros.
 // ---------------------------------------------------------------------------------------
 template <int FMT>
@@ -227,46 +228,43 @@ __device__ __forceinline__ void quantize8(const float x[8], uint32_t code[8], fl
   }
 }
 
-// The 4 threads of lane record `rec` (slice s = lane % 4) write it.
+// Threads s = 0..3 of a lane record hold its 24-byte E2M3 run as 48 bits each (r: two 24-bit
+// runs); they write its six dwords, 0-3 in the fragment's 16-byte plane (lane l) and 4-5 in
+// the 8-byte one.  An even thread's second dword takes the low 16 bits of its odd partner.
+__device__ __forceinline__ void store_e2m3_run(uint8_t* __restrict__ f, int l, int s, const uint32_t r[2]) {
+  const uint32_t w0 = r[0] | (r[1] << 24), w1 = r[1] >> 8;  // the 48 bits: w0, low half of w1
+  const uint32_t p0 = dpp_u32<kDppXor1>(w0);
+  const bool odd = (s & 1) != 0;
+  // dword 0, 2, 3, 5 of threads 0, 1, 2, 3
+  uint8_t* at = s == 3 ? f + kHiTail + l * 8 + 4 : f + l * 16 + (s == 0 ? 0 : s == 1 ? 8 : 12);
+  *reinterpret_cast<uint32_t*>(at) = odd ? (w0 >> 16) | (w1 << 16) : w0;
+  if (!odd)  // dword 1 or 4
+    *reinterpret_cast<uint32_t*>(s == 0 ? f + l * 16 + 4 : f + kHiTail + l * 8) = w1 | (p0 << 16);
+}
+
+__device__ __forceinline__ uint32_t codes_to_bytes(const uint32_t c[4]) {
+  return c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
+}
+
+// The 4 threads of lane record `rec` (slice s = lane % 4) write it; tab: the HiF4 split table.
 template <int FMT>
 __device__ __forceinline__ void store_record8(uint8_t* __restrict__ frag, uint8_t* __restrict__ fsc,
                                               int64_t rec, int s, const uint32_t code[8],
-                                              uint32_t scale_byte, int c1, const int b[2]) {
+                                              uint32_t scale_byte, int c1, const int b[2], const uint4* tab) {
   if constexpr (FMT == kMX) {
     uint32_t w = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) w |= code[i] << (4 * i);
     reinterpret_cast<uint32_t*>(frag + rec * 16)[s] = w;
   } else {
-    // 8 six-bit fields = 48 bits each of hi and lo; record = hi bits [0,192) then lo.  Each
-    // 48-bit run is built as two 24-bit runs of 4 fields (one level-3 shift each) in 32-bit
-    // words.
+    uint8_t* f = frag + (rec >> 6) * kHiAFrag;
+    const int l = (int)(rec & 63), m3 = 3 * (c1 & 3);
     uint32_t rh[2], rl[2];
-    const uint32_t q2 = (4u + ((uint32_t)c1 & 3u)) * 0x00010001u;
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const uint32_t nb = code[4 * hh] | (code[4 * hh + 1] << 8) | (code[4 * hh + 2] << 16) | (code[4 * hh + 3] << 24);
-      hif4_split4(nb, q2, (uint32_t)b[hh], rh[hh], rl[hh]);
-    }
-    const uint64_t h = rh[0] | ((uint64_t)rh[1] << 24), l = rl[0] | ((uint64_t)rl[1] << 24);
-    // thread s writes record dwords 3s .. 3s+2: hi of slices 0,1 / hi of 2,3 / lo of 0,1 /
-    // lo of 2,3, i.e. 96 bits assembled from two slices' 48-bit runs
-    const int lane = __lane_id();
-    const int base = lane & ~3, src = base + 2 * (s & 1);
-    const uint32_t hl0 = __shfl((uint32_t)h, src, 64), hh0 = __shfl((uint32_t)(h >> 32), src, 64);
-    const uint32_t hl1 = __shfl((uint32_t)h, src + 1, 64), hh1 = __shfl((uint32_t)(h >> 32), src + 1, 64);
-    const uint32_t ll0 = __shfl((uint32_t)l, src, 64), lh0 = __shfl((uint32_t)(l >> 32), src, 64);
-    const uint32_t ll1 = __shfl((uint32_t)l, src + 1, 64), lh1 = __shfl((uint32_t)(l >> 32), src + 1, 64);
-    const bool lo_part = s >= 2;
-    const uint64_t p0 = ((uint64_t)(lo_part ? lh0 : hh0) << 32) | (lo_part ? ll0 : hl0);  // 48 bits
-    const uint64_t p1 = ((uint64_t)(lo_part ? lh1 : hh1) << 32) | (lo_part ? ll1 : hl1);
-    const uint32_t d0 = (uint32_t)p0;
-    const uint32_t d1 = (uint32_t)(p0 >> 32) | ((uint32_t)p1 << 16);
-    const uint32_t d2 = (uint32_t)(p1 >> 16);
-    uint32_t* w = reinterpret_cast<uint32_t*>(frag + rec * 48) + 3 * s;
-    w[0] = d0;
-    w[1] = d1;
-    w[2] = d2;
+    for (int hh = 0; hh < 2; ++hh) hif4_split4(codes_to_bytes(code + 4 * hh), tab[m3 + b[hh]], rh[hh], rl[hh]);
+    store_e2m3_run(f, l, s, rh);
+    reinterpret_cast<uint32_t*>(f + kHiLo + l * 16)[s] = rl[0] | (rl[1] << 16);
+    scale_byte = hif4_act_scale(scale_byte);
   }
   if (s == 0) fsc[rec] = (uint8_t)scale_byte;
 }
@@ -564,7 +562,8 @@ __device__ __forceinline__ void residual_frag_tile(
     const uint16_t* __restrict__ X, int64_t m, int64_t d, int64_t ldx, int64_t nkb,
     uint8_t* __restrict__ fx, uint8_t* __restrict__ fsx, uint8_t* __restrict__ fr,
     uint8_t* __restrict__ fsr, double* __restrict__ partials, int nm_keep, const Producer& prod,
-    int64_t t, int64_t kb, uint32_t* ehist_lds, double* rowsq_lds, double* __restrict__ bkeys) {
+    int64_t t, int64_t kb, uint32_t* ehist_lds, double* rowsq_lds, double* __restrict__ bkeys,
+    const uint4* tab) {
   const int64_t f = t * nkb + kb;  // fragment index
   const int tid = threadIdx.x;
   const int rr = tid >> 3, half = (tid >> 2) & 1, s = tid & 3;
@@ -598,7 +597,7 @@ __device__ __forceinline__ void residual_frag_tile(
   float val[8];
   int c1, b[2], b2;
   quantize8<FMT>(x, code, val, scale_byte, c1, b, b2);
-  store_record8<FMT>(fx, fsx, rec, s, code, scale_byte, c1, b);
+  store_record8<FMT>(fx, fsx, rec, s, code, scale_byte, c1, b, tab);
   if constexpr (MODE != kResidNone) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] -= val[i];  // dX, exact in float32
@@ -643,7 +642,7 @@ __device__ __forceinline__ void residual_frag_tile(
           hist_add_copies(ehist_lds, 256, (__float_as_uint(val[i]) >> 23) & 255u, row < m && col0 < d);
       }
     } else {
-      store_record8<FMT>(fr, fsr, rec, s, code, scale_byte, c1, b);
+      store_record8<FMT>(fr, fsr, rec, s, code, scale_byte, c1, b, tab);
     }
   }
 }
@@ -662,16 +661,17 @@ __global__ __launch_bounds__(256) void residual_frag_kernel(
     int nm_keep, Producer prod, double* __restrict__ bkeys) {
   __shared__ uint32_t lh[MODE == kResidDense ? kLdsCopies * 257 : 1];  // hist.h copies of 256 bins
   __shared__ double rowsq[MODE == kResidDense ? 64 : 1];  // block keys: the tile's row sums
+  __shared__ uint4 tab[FMT == kHI ? kHiSplitEntries : 1];
   const bool counting = MODE == kResidDense && ehist != nullptr;
-  if (counting) {
+  if constexpr (FMT == kHI) hif4_load_split_tab(tab);
+  if (counting)
     for (int i = threadIdx.x; i < kLdsCopies * 257; i += 256) lh[i] = 0u;
-    __syncthreads();
-  }
+  if (FMT == kHI || counting) __syncthreads();
   const int64_t mtiles = (m + 31) / 32;
   for (int64_t t = blockIdx.y; t < mtiles; t += gridDim.y)
     residual_frag_tile<FMT, MODE, VEC, PROD>(X, m, d, ldx, nkb, fx, fsx, fr, fsr, partials, nm_keep,
                                                prod, t, blockIdx.x, counting ? lh : nullptr, rowsq,
-                                               MODE == kResidDense ? bkeys : nullptr);
+                                               MODE == kResidDense ? bkeys : nullptr, tab);
   if (counting) {
     __syncthreads();
     const uint32_t c = hist_sum_copies(lh, 256, threadIdx.x);
@@ -690,25 +690,14 @@ __global__ __launch_bounds__(256) void residual_frag_kernel(
 // missing half of an MXFP4 K step) and columns past C quantize zeros.
 // ---------------------------------------------------------------------------------------
 
-// HiF4 weight-side record: the 4 threads of lane record `rec` hold 8 BF6 E3M2 fields each
-// (48 bits); threads s and s+1 (s even) write record dwords 3s/2 .. 3s/2+2.
-__device__ __forceinline__ void store_record8_e3m2(uint8_t* __restrict__ frag, uint8_t* __restrict__ fsc,
-                                                   int64_t rec, int s, const uint32_t code[8],
-                                                   uint32_t scale_byte, const int b[2]) {
+// HiF4 weight-side record: the 4 threads of lane record `rec` hold 8 E2M3 fields each.
+__device__ __forceinline__ void store_record8_weight(uint8_t* __restrict__ frag, uint8_t* __restrict__ fsc,
+                                                     int64_t rec, int s, const uint32_t code[8],
+                                                     uint32_t scale_byte, const int b[2]) {
   uint32_t r[2];  // two 24-bit runs of 4 fields
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh)
-    r[hh] = hif4_e3m2x4(code[4 * hh] | (code[4 * hh + 1] << 8) | (code[4 * hh + 2] << 16) | (code[4 * hh + 3] << 24),
-                        (uint32_t)b[hh]);
-  const uint64_t h = r[0] | ((uint64_t)r[1] << 24);
-  const uint32_t plo = __shfl_xor((uint32_t)h, 1, 64), phi = __shfl_xor((uint32_t)(h >> 32), 1, 64);
-  if ((s & 1) == 0) {
-    const uint64_t p1 = ((uint64_t)phi << 32) | plo;  // the odd partner's 48 bits
-    uint32_t* w = reinterpret_cast<uint32_t*>(frag + rec * 24) + 3 * (s >> 1);
-    w[0] = (uint32_t)h;
-    w[1] = (uint32_t)(h >> 32) | ((uint32_t)p1 << 16);
-    w[2] = (uint32_t)(p1 >> 16);
-  }
+  for (int hh = 0; hh < 2; ++hh) r[hh] = hif4_e2m3x4(codes_to_bytes(code + 4 * hh), (uint32_t)b[hh]);
+  store_e2m3_run(frag + (rec >> 6) * kHiBFrag, (int)(rec & 63), s, r);
   if (s == 0) fsc[rec] = (uint8_t)scale_byte;
 }
 
@@ -722,7 +711,8 @@ __device__ __forceinline__ void quant_cols_frag_tile(const uint16_t* __restrict_
                                                      int64_t C, int64_t ld, int64_t nkb, int64_t nt,
                                                      uint8_t* __restrict__ frag, uint8_t* __restrict__ fsc,
                                                      uint8_t* __restrict__ rfrag, uint8_t* __restrict__ rfsc,
-                                                     uint16_t* tile, int64_t T, int64_t kb) {
+                                                     uint16_t* tile, int64_t T, int64_t kb,
+                                                     const uint4* tab) {
   constexpr int kPitch = 128 + 2;  // bf16 per LDS row (padding spreads the column reads)
   const int64_t r0 = kb * 64, c0 = T * 128;
   const int tid = threadIdx.x;
@@ -760,8 +750,8 @@ __device__ __forceinline__ void quant_cols_frag_tile(const uint16_t* __restrict_
     int c1, b[2], b2;
     quantize8<FMT>(v, code, val, scale_byte, c1, b, b2);
     const int64_t rec = (t * nkb + kb) * 64 + rr + 32 * half;
-    if constexpr (PMODE == kPackHiB) store_record8_e3m2(frag, fsc, rec, s, code, scale_byte, b);
-    else store_record8<FMT>(frag, fsc, rec, s, code, scale_byte, c1, b);
+    if constexpr (PMODE == kPackHiB) store_record8_weight(frag, fsc, rec, s, code, scale_byte, b);
+    else store_record8<FMT>(frag, fsc, rec, s, code, scale_byte, c1, b, tab);
   }
   if constexpr (DUAL) {
     const int64_t rkb = (C + 63) / 64, rnt = (R + 31) / 32;  // row operand: K steps, row tiles
@@ -782,7 +772,7 @@ __device__ __forceinline__ void quant_cols_frag_tile(const uint16_t* __restrict_
       float val[8];
       int c1, b[2], b2;
       quantize8<FMT>(v, code, val, scale_byte, c1, b, b2);
-      store_record8<FMT>(rfrag, rfsc, (t * rkb + k) * 64 + rr + 32 * half, s, code, scale_byte, c1, b);
+      store_record8<FMT>(rfrag, rfsc, (t * rkb + k) * 64 + rr + 32 * half, s, code, scale_byte, c1, b, tab);
     }
   }
 }
@@ -797,10 +787,12 @@ __global__ __launch_bounds__(256) void quant_cols_frag_kernel(const uint16_t* __
                                                               uint8_t* __restrict__ rfsc) {
   constexpr int kPitch = 128 + 2;
   __shared__ uint16_t tile[64 * kPitch];
+  __shared__ uint4 tab[FMT == kHI ? kHiSplitEntries : 1];
+  if constexpr (FMT == kHI) hif4_load_split_tab(tab);  // published by the first tile's barrier
   const int64_t ngroups = (nt + 3) / 4;
   for (int64_t T = blockIdx.y; T < ngroups; T += gridDim.y) {
     if (T != blockIdx.y) __syncthreads();  // the previous group's reads of the tile are done
-    quant_cols_frag_tile<FMT, PMODE, VEC, DUAL>(x, R, C, ld, nkb, nt, frag, fsc, rfrag, rfsc, tile, T, blockIdx.x);
+    quant_cols_frag_tile<FMT, PMODE, VEC, DUAL>(x, R, C, ld, nkb, nt, frag, fsc, rfrag, rfsc, tile, T, blockIdx.x, tab);
   }
 }
 

@@ -780,6 +780,8 @@ __global__ __launch_bounds__(kThreads) void uapply_kernel(uint8_t* __restrict__ 
                                                           uint8_t* __restrict__ fscale) {
   __shared__ uint32_t ch[4];
   __shared__ uint64_t wsum[kThreads / 64];
+  __shared__ uint4 tab[PMODE == kPackHiA ? kHiSplitEntries : 1];
+  if constexpr (PMODE == kPackHiA) hif4_load_split_tab(tab);  // published by load_choice's barrier
   const int64_t w0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * kWordsPerThread;
   const bool in = w0 < m * (d / 8);
   ThreadWords tw{};
@@ -830,15 +832,15 @@ __global__ __launch_bounds__(kThreads) void uapply_kernel(uint8_t* __restrict__ 
     const int half = (int)((j / 32) & 1u);
     const uint32_t sc = tw.sc;  // the scale of this thread's block, loaded above
     const int64_t rec = ((int64_t)(row / 32) * nkb + kb) * 64 + (row & 31) + 32 * half;
-    store_frag_record<PMODE>(frag, fscale, rec, v, sc, half);
+    store_frag_record<PMODE>(frag, fscale, rec, v, sc, half, tab);
     const uint4 z = make_uint4(0, 0, 0, 0);
     if ((d & 63) == 32 && j + 32 == (uint32_t)d)  // the missing half K step: zero codes, scale 0
-      store_frag_record<PMODE>(frag, fscale, rec + 32, z, 0u, 1);
+      store_frag_record<PMODE>(frag, fscale, rec + 32, z, 0u, 1, tab);
     if (row + 1 == (uint32_t)m)  // rows past m inside the last row tile: zero records
       for (uint32_t r = row + 1; r % 32 != 0; ++r) {
         const int64_t pr = ((int64_t)(r / 32) * nkb + kb) * 64 + (r & 31);
-        store_frag_record<PMODE>(frag, fscale, pr + 32 * half, z, 0u, half);
-        if ((d & 63) == 32 && j + 32 == (uint32_t)d) store_frag_record<PMODE>(frag, fscale, pr + 32, z, 0u, 1);
+        store_frag_record<PMODE>(frag, fscale, pr + 32 * half, z, 0u, half, tab);
+        if ((d & 63) == 32 && j + 32 == (uint32_t)d) store_frag_record<PMODE>(frag, fscale, pr + 32, z, 0u, 1, tab);
       }
   }
 }
