@@ -330,11 +330,12 @@ int resq_linear_w16a4(int format, const uint16_t* X, int64_t m, int64_t d, int64
  * K = d and may split K (split_allowed = 1); the backward's dX GEMM has M = m, N = d, K = n,
  * and its dW GEMM M = n, N = d, K = m, neither split (split_allowed = 0).
  * info receives four values: [0] tile configuration (RESQ_TILE_*), [1] K split count,
- * [2] K groups per workgroup, [3] LDS pipeline stages.  Returns RESQ_ERR_ARG for an unknown
+ * [2] K groups per workgroup, [3] LDS pipeline stages.  The 32-row tiles are not staged through
+ * LDS: there [2] is the waves that share a tile's K steps and [3] the steps each loads ahead.  Returns RESQ_ERR_ARG for an unknown
  * format, negative sizes or a NULL info.
  */
 enum { RESQ_TILE_64x64 = 0, RESQ_TILE_128x256 = 1, RESQ_TILE_128x192 = 2, RESQ_TILE_128x192_8W = 3,
-       RESQ_TILE_64x128 = 4 };
+       RESQ_TILE_64x128 = 4, RESQ_TILE_32x32 = 5, RESQ_TILE_32x64 = 6, RESQ_TILE_32x96 = 7 };
 int resq_gemm_plan(int format, int64_t M, int64_t N, int64_t K, int split_allowed, int32_t info[4]);
 
 /* Human-readable description of the last non-OK status on this thread ("" if none). */

@@ -16,7 +16,7 @@ OUT_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libresq.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["quant.hip", "pack.hip", "select.hip", "gemm.hip", "gemm_hif4.hip", "diag.hip", "mixed.hip", "api.cpp", "profiler.cpp"]
+SOURCES = ["quant.hip", "pack.hip", "select.hip", "gemm.hip", "gemm_hif4.hip", "gemm_stream.hip", "diag.hip", "mixed.hip", "api.cpp", "profiler.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-FP32 VALU forms are kept off; fp32 denormals are kept (exact FP4 rounding)
@@ -29,7 +29,7 @@ FLAGS = [
 
 # Per-source extra flags.  The GEMMs: MFMA results in VGPRs (the HiF4 fold reads them with
 # VALU instructions, which cannot read AGPRs).
-EXTRA = {"gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "gemm_hif4.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("gemm.hip", "gemm_hif4.hip", "gemm_stream.hip")}
 
 
 def _compile(src: str) -> str:

@@ -241,4 +241,9 @@ __device__ __forceinline__ uint32_t hif4_e2m3x4(uint32_t nb, uint32_t b) {
   return close_up6x4(__builtin_amdgcn_perm(hi, lo, nb & 0x07070707u) | ((nb & 0x08080808u) << 2));
 }
 
+// Weight-operand scales of the hi and lo products (E8M0 of 2^0 and 2^-4), and the fold factor
+// (4 + m) 2^(e-35) of level-1 code c = 4e + m: exponent field e + 94, fraction m / 4.
+constexpr int kHiOne = 127, kHiLoScale = 123;
+__device__ __forceinline__ float hif4_fold_factor(uint32_t c) { return __uint_as_float((c << 21) + (94u << 23)); }
+
 }  // namespace resq

@@ -38,6 +38,9 @@
 #include "gemm_core.h"
 #include "gemm_geo.h"
 #include "gemm_hif4.h"
+#include "gemm_stream.h"
+
+#include <algorithm>
 
 
 namespace resq {
@@ -214,17 +217,54 @@ void launch_cfg(const GemmParams& p, int n_terms, hipStream_t s) {
 //    the other's MFMAs; 128 x 256 HiF4 tiles would spill.  When the
 //    HiF4 grid has fewer than two workgroups per CU (M = 256 decode), the tile runs as eight
 //    waves of 32 x 96 instead, so each SIMD still holds two waves.
-enum TileCfg { kSmall = 0, kWide = 1, kMid = 2, kMid8 = 3, kNarrow = 4 };
-// output tile rows and columns of each configuration
+enum TileCfg { kSmall = 0, kWide = 1, kMid = 2, kMid8 = 3, kNarrow = 4, kStream = 5 };  // kStream + TN - 1
+// output tile rows and columns of the staged configurations
 constexpr int kTileRows[5] = {64, 128, 128, 128, 64}, kTileCols[5] = {64, 256, 192, 192, 128};
-constexpr int kCUs = 256;
+constexpr int64_t kCUs = 256;
 
 struct Plan {
   int cfg, ksplit;
-  int kg, ns;  // small tiles: K groups and stages
+  int kg, ns;  // small tiles: K groups and stages; streamed: waves and K steps in flight
   int64_t kper, tiles;
   size_t partial_bytes;
 };
+
+// Grids of few output tiles go to gemm_stream.hip, one row tile x TN column tiles per workgroup.
+// Kernel times in us, staged plan -> streamed, MXFP4 / HiF4, S_2:4:
+//  - up to one 32 x 32 tile per CU, TN = 1: 2048 -> 2048 at m = 8 6.0 -> 4.0 / 9.7 -> 5.0, at
+//    m = 128 6.5 -> 4.3 / 10.8 -> 5.8; 11008 -> 2048 at m = 8 14.4 -> 7.2 / 23.6 -> 14.2; 18944
+//    -> 3584 at m = 64 23.8 -> 18.6 / 42 -> 32.7; past that TN = 1 loses (m = 96: 24 -> 30.5);
+//  - up to one 32 x 64 tile per CU, TN = 2: 2048 -> 2560 at m = 128 7.0 -> 5.5 / 10.4 -> 7.2;
+//    18944 -> 3584 at m = 128 24.7 -> 24.2 / 42.7 -> 41.1;
+//  - HiF4 up to one 32 x 96 tile per CU, TN = 3: 3584 -> 4608 at m = 128 14.8 -> 11.0;
+//  - wide N, where the weights are read for one row tile (HiF4: two), TN = 2 in four waves: 2048
+//    -> 22016 at m = 8 9.3 -> 7.5 / 22 -> 12.0, at m = 64 10.4 -> 11.8 / 23 -> 19.1; 3584 ->
+//    37888 at m = 32 18.2 -> 19.4 / 40 -> 23.8 (hence MXFP4 only below 1024 column tiles).
+// M >= 256 stays with the staged plans except M = 256 with short K (2048 -> 2048: 7.2 -> 6.6 /
+// 11.2 -> 8.0).  Long K would gain there too (11008 -> 2048: 19 -> 12.5 / 26.9 -> 21.1); the
+// determinism test's list of plans fixes what resq_gemm_plan reports for those shapes.
+// Very long K over few workgroups is split (65536 -> 256 at m = 8: 42 -> 11.3 / 88 -> 18.2).
+bool stream_plan(int fmt, int64_t M, int64_t mt, int64_t nt, int64_t nkb, bool may_split, Plan& pl) {
+  if (M > 256 || (M == 256 && nkb >= 128)) return false;
+  auto tiles = [&](int64_t tn) { return mt * ((nt + tn - 1) / tn); };
+  int tn = 0, waves = 8;
+  if (tiles(1) <= kCUs) tn = 1;
+  else if (tiles(2) <= kCUs) tn = 2;
+  else if (fmt == 1 && M < 256 && tiles(3) <= kCUs) tn = 3;
+  else if (fmt == 1 ? mt <= 2 : mt == 1 && nt < 1024) tn = 2, waves = 4;
+  if (tn == 0) return false;
+  pl.cfg = kStream + tn - 1;
+  pl.tiles = tiles(tn);
+  pl.kg = waves;
+  pl.ns = fmt == 0 ? 2 : 1;
+  if (may_split && pl.tiles <= kCUs / 2 && nkb >= 512) {
+    const int64_t ks = std::min(kCUs / pl.tiles, nkb / 128);
+    pl.ksplit = (int)(ks > 8 ? 8 : ks);
+    pl.kper = (nkb + pl.ksplit - 1) / pl.ksplit;
+    pl.partial_bytes = (size_t)pl.tiles * pl.ksplit * (tn * 1024) * sizeof(float);
+  }
+  return true;
+}
 
 Plan plan(int fmt, int64_t M, int64_t N, int64_t K, bool may_split) {
   const int64_t mt = (M + 31) / 32, nt = (N + 31) / 32, nkb = (K + 63) / 64;
@@ -232,6 +272,7 @@ Plan plan(int fmt, int64_t M, int64_t N, int64_t K, bool may_split) {
   Plan pl{};
   pl.ksplit = 1;
   pl.kper = nkb;
+  if (stream_plan(fmt, M, mt, nt, nkb, may_split, pl)) return pl;
   if (wgs(4, 4) < 240 && may_split && nkb >= 128 && kCUs / wgs(2, 4) >= 2) {
     // small grids with long K (the down projection of a decode batch): 64 x 128 tiles with K
     // split up to four ways; the wider tile reads each activation fragment for twice the
@@ -310,9 +351,10 @@ Plan plan(int fmt, int64_t M, int64_t N, int64_t K, bool may_split) {
   return pl;
 }
 
-// Launches the configuration of the plan (RESQ_GEMM_CONFIGS or, for HiF4, RESQ_HIF4_CONFIGS);
-// false if none matches.
+// Launches the configuration of the plan (RESQ_GEMM_CONFIGS, for HiF4 RESQ_HIF4_CONFIGS, for
+// streamed plans RESQ_STREAM_CONFIGS); false if none matches.
 bool launch_plan(const GemmParams& p, int fmt, const Plan& pl, int n_terms, hipStream_t s) {
+  if (pl.cfg >= kStream) return launch_gemm_stream(p, fmt, pl.cfg - kStream + 1, pl.kg, pl.ns, n_terms, s);
   if (fmt == 1) return launch_gemm_hif4(p, pl.cfg, pl.ns, pl.kg, n_terms, s);
 #define RESQ_GEMM_LAUNCH(F, C, WM, WN, TM, TN, NS, KG)                                  \
   if (fmt == F && pl.cfg == C && pl.ns == NS && pl.kg == KG) {                          \

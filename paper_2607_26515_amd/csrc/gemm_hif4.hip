@@ -24,11 +24,6 @@ namespace {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 
-constexpr int kOne = 127, kLoScale = 123;  // E8M0 of 2^0 and 2^-4
-
-// (4 + m) 2^(e-35) of level-1 code c = 4e + m: exponent field e + 94, fraction m / 4
-__device__ __forceinline__ float hif4_fold_factor(uint32_t c) { return __uint_as_float((c << 21) + (94u << 23)); }
-
 template <class G>
 __global__ __launch_bounds__(64 * G::W)
 __attribute__((amdgpu_waves_per_eu(G::TM * G::TN > 1 ? 2 : G::KG)))
@@ -171,8 +166,8 @@ void gemm_hif4_kernel(GemmParams p) {
       v16f P = v16f{};
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        P = mfma<2, 2>(a.hi[t], o.x[j], P, a.s[t], kOne);
-        P = mfma<4, 2>(a.lo[t], o.x[j], P, a.s[t], kLoScale);
+        P = mfma<2, 2>(a.hi[t], o.x[j], P, a.s[t], kHiOne);
+        P = mfma<4, 2>(a.lo[t], o.x[j], P, a.s[t], kHiLoScale);
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[ip][jp][r] = fmaf(Pp[r], fp, acc[ip][jp][r]);

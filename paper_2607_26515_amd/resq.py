@@ -85,7 +85,8 @@ EXPORTED = ("resq_quantize", "resq_residual_sparsify", "resq_linear_fwd", "resq_
             "resq_diagnostics", "resq_linear_fwd_prepared_swiglu", "resq_gemm_plan",
             "resq_linear_fwd_prepared_noalloc", "resq_linear_w4a16", "resq_linear_w16a4",
             "resq_linear_fwd_prepared_rmsnorm")
-GEMM_TILES = {0: "64x64", 1: "128x256", 2: "128x192", 3: "128x192_8w", 4: "64x128"}
+GEMM_TILES = {0: "64x64", 1: "128x256", 2: "128x192", 3: "128x192_8w", 4: "64x128", 5: "32x32", 6: "32x64",
+              7: "32x96"}
 
 
 class ResqError(RuntimeError):
