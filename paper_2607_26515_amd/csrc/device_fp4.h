@@ -117,66 +117,61 @@ __device__ __forceinline__ void mx_value2(uint32_t codes2, float scale, float& v
 // Smallest code c with 1.75 * s1(c) >= A (saturating at 255), for a magnitude A (finite, +0 or
 // positive).  For A in [2^ea, 2^(ea+1)) the values 1.75 * s1 of codes 4(ea+30)+1 .. +4 are
 // {35, 42, 49, 56, 63} 2^(ea-5), i.e. mantissas 1.09375, 1.3125, 1.53125, 1.75 and above 1.875,
-// so c is that base code plus the number of the first four that A's mantissa exceeds, read
-// straight from its exponent and fraction fields.  Subnormal A (ea < -126) and every A below
-// 2^-31 give a negative count, clamped to code 0.
+// so c is that base code plus the number of the first four that A's mantissa exceeds.  On the
+// pattern u - 1 "exceeds" is "reaches", and in units of 2^18 the four fractions are 3, 10, 17 and
+// 24: their count for a five-bit fraction f is (585 f + 2344) >> 12.  (u a power of two borrows
+// from the exponent and counts four there; u = 0 gives a negative count.)  Every A below 2^-31
+// gives a negative count, clamped to code 0.
 __device__ __forceinline__ int hif4_c1(float A) {
-  const uint32_t u = __float_as_uint(A);
-  const int E = (int)(u >> 23);  // biased exponent ea + 127
-  const uint32_t f = u & 0x7FFFFFu;
-  const int c = 4 * E - 387 + (f > 0x0C0000u) + (f > 0x280000u) + (f > 0x440000u) + (f > 0x600000u);
+  const int v = (int)__float_as_uint(A) - 1;
+  const int c = 4 * (v >> 23) + ((((v >> 18) & 31) * 585 + 2344) >> 12) - 387;
   return c < 0 ? 0 : (c > 255 ? 255 : c);
 }
 
-// 1.75 * s1 / 2 * 2^-shift = 7 (4+m) 2^(e-36-shift): the "fits at half the scale" threshold.
-__device__ __forceinline__ float hif4_half_fit(int c1, int shift) {
-  return ldexpf((float)(7 * (4 + (c1 & 3))), (c1 >> 2) - 36 - shift);
-}
-
-// The midpoints of the element grid of level-1 code c1 that hif4_k compares with, in units of
-// 2^(e-36-b): q, 3q, 7q and 11q, and the step 2q (q = 4+m; small integers, exact).
-struct Hif4Mid {
-  float q, q2, q3, q7, q11;
+// The element grid of level-1 code c1 and shift b: its step (4+m) 2^(e-35-b) (exact and normal:
+// at least 4 * 2^-37) and the step's reciprocal, fl(1 / (4+m)) times the exact power of two.
+struct Hif4Grid {
+  float step, inv;
 };
-__device__ __forceinline__ Hif4Mid hif4_mid(int c1) {
-  const float q = (float)(4 + (c1 & 3));
-  Hif4Mid t{q, 2.f * q, 3.f * q, 7.f * q, 11.f * q};
-  // Kept opaque: the optimiser would otherwise turn the per-element choice between 3q and 11q
-  // into an integer multiply and a conversion.
-  asm("" : "+v"(t.q3), "+v"(t.q11));
-  return t;
+__device__ __forceinline__ float hif4_inv_q(int c1) {
+  const int m = c1 & 3;
+  return m == 0 ? 0.25f : m == 1 ? 0.2f : m == 2 ? 1.0f / 6.0f : 1.0f / 7.0f;
 }
+__device__ __forceinline__ Hif4Grid hif4_grid(int c1, float inv_q, int b) {
+  const int p = (c1 >> 2) - 35 - b;
+  return Hif4Grid{ldexpf((float)(4 + (c1 & 3)), p), ldexpf(inv_q, -p)};
+}
+// The "fits at half the scale" threshold 1.75 * s1 / 2 * 2^-b of a group, from the step of
+// shift b: 7 (4+m) 2^(e-36-b) = 3.5 step (exact).
+__device__ __forceinline__ float hif4_half_fit(float step) { return 3.5f * step; }
 
-// Magnitude k (0..7) of |x| on the grid k/4 * s, s = s1 2^-b: nearest, ties to even k.
-// On the rescaled y = |x| 2^(36+b-e) the midpoint between j and j+1 is (2j+1) q; a tie goes to
-// the even neighbour, so y must exceed the midpoint above an even j and reach the one above an
-// odd j.  k is the number of midpoints passed, found by a three-step binary search: 3|4 (7q),
-// then 1|2 (3q) or 5|6 (11q), then the midpoint above the even k so far, 2q further up or
-// down.  NaN passes none (k = 0), +inf all (k = 7).
-__device__ __forceinline__ uint32_t hif4_k(float x, int c1, int b, const Hif4Mid& t) {
-  const float y = ldexpf(fabsf(x), 36 + b - (c1 >> 2));
-  const bool h4 = y >= t.q7;
-  const float t2 = h4 ? t.q11 : t.q3;
-  const bool h2 = y >= t2;
-  const float t1 = t2 + (h2 ? t.q2 : -t.q2);
-  const bool h1 = y > t1;
-  return (h4 ? 4u : 0u) + (h2 ? 2u : 0u) + (h1 ? 1u : 0u);
+// x on that grid: the signed integer k (-7 .. 7, with x's sign when zero) nearest to x / step,
+// ties to even k, saturating.  inv is the correctly rounded reciprocal, so one residual step
+// rounds the quotient correctly; and since the grid's midpoints (2j+1)/2 have few bits and
+// float32 values around a midpoint times the step are at least half a place apart in the quotient
+// ((4+m) < 8), a quotient equals a midpoint exactly when x does, so rounding it again to
+// an integer is the rounding of x / step itself.  Checked against the comparison with every
+// midpoint for all finite float32 x, every m and b (host emulation).
+__device__ __forceinline__ float hif4_round(float x, const Hif4Grid& g) {
+  const float lim = 7.f * g.step;
+  const float xc = __builtin_amdgcn_fmed3f(x, -lim, lim);
+  const float y = xc * g.inv;
+  return __builtin_rintf(fmaf(-fmaf(y, g.step, -xc), g.inv, y));  // in this form -0 stays -0
+}
+// The 4-bit codes of four elements, one per byte (high nibbles zero): |k| and the sign of x.
+__device__ __forceinline__ uint32_t hif4_code_bytes(const float k[4], const float x[4]) {
+  uint32_t n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[0]), 0u, 0u);
+  n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[1]), 1u, n);
+  n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[2]), 2u, n);
+  n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[3]), 3u, n);
+  const uint32_t s = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x0C0C0703u) |
+                     __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07030C0Cu);
+  return n | ((s >> 4) & 0x08080808u);
 }
 
 __device__ __forceinline__ float hif4_value(uint32_t code, int c1, int b) {
   const float v = ldexpf((float)((code & 7) * (4 + (c1 & 3))), (c1 >> 2) - 35 - b);
   return (code & 8) ? -v : v;
-}
-
-// The grid step of level-1 code c1 and shift b, (4+m) 2^(e-35-b) (exact and normal: at least
-// 4 * 2^-37), and the element value k * step carrying the sign of x, which is the code's sign
-// (k = 0 included: a signed zero); k * step <= 7 * 7 * 2^28 is exact.  The quantizers use this
-// form: one conversion, one multiply and one sign insertion per element.
-__device__ __forceinline__ float hif4_step(int c1, int b) {
-  return ldexpf((float)(4 + (c1 & 3)), (c1 >> 2) - 35 - b);
-}
-__device__ __forceinline__ float hif4_signed_value(uint32_t k, float step, float x) {
-  return copysignf((float)k * step, x);
 }
 
 // Compress the even bits of a 16-bit value into 8 bits.

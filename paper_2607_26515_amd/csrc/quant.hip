@@ -44,26 +44,6 @@ __device__ __forceinline__ void store_scale(void* scales, int64_t row, int64_t K
 }
 
 // ---------------------------------------------------------------------------------------
-// Q along rows: one lane per 4 elements, grid (ceil(cols/1024), rows)
-// ---------------------------------------------------------------------------------------
-template <int FMT, bool F32, bool VEC>
-__global__ __launch_bounds__(kThreads) void quant_rows_kernel(const void* __restrict__ x,
-                                                              int64_t rows, int64_t cols,
-                                                              int64_t ld,
-                                                              uint8_t* __restrict__ codes,
-                                                              void* __restrict__ scales) {
-  const int64_t j4 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (4 * j4 >= cols) return;  // whole blocks drop out together (cols % block == 0)
-  for (int64_t row = blockIdx.y; row < rows; row += gridDim.y) {
-    float v[4];
-    load4<F32, VEC>(x, row * ld + 4 * j4, v);
-    const Quad q = quantize_quad<FMT>(v);
-    *reinterpret_cast<uint16_t*>(codes + row * (cols / 2) + 2 * j4) = (uint16_t)pack_quad_codes(q.code);
-    store_scale<FMT>(scales, row, cols, j4, q.scale);
-  }
-}
-
-// ---------------------------------------------------------------------------------------
 // Q along columns (transposed output): 64 x 64 tiles staged through LDS
 // ---------------------------------------------------------------------------------------
 template <int FMT, bool F32>
@@ -184,48 +164,97 @@ __global__ __launch_bounds__(kThreads) void residual_kernel(
 // (MXFP4: 16 contiguous bytes; HiF4: pieces of the fragment's planes, gemm_hif4_geo.h).  Rows past m, and the missing half of an MXFP4 K step
 // when d % 64 == 32, quantize zeros.
 // ---------------------------------------------------------------------------------------
+// Eight consecutive elements of one lane, quantized.
 template <int FMT>
-__device__ __forceinline__ void quantize8(const float x[8], uint32_t code[8], float val[8],
-                                          uint32_t& scale_byte, int& c1, int b[2], int& b2o) {
-  float a = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a = fmaxf(a, fabsf(x[i]));
-  if constexpr (FMT == kMX) {
-    const int E = mx_exponent(group_max<4>(a));
-    scale_byte = (uint32_t)(E + 127);
-    c1 = 0;
-    b[0] = b[1] = 0;
-    b2o = 0;
-    const float sc = mx_scale_f32(E);
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-      const uint32_t c2 = mx_code2(x[i], x[i + 1], sc);
-      code[i] = c2 & 15u;
-      code[i + 1] = c2 >> 4;
-      mx_value2(c2, sc, val[i], val[i + 1]);
-    }
-  } else {
-    c1 = hif4_c1(group_max<8>(a));
-    scale_byte = (uint32_t)c1;
-    const float fit0 = hif4_half_fit(c1, 0), fit1 = hif4_half_fit(c1, 1);
-    const int b2 = a <= fit0 ? 1 : 0;  // this lane's 8 elements are one level-2 group
-    b2o = b2;
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      float a4 = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) a4 = fmaxf(a4, fabsf(x[4 * hh + e]));
-      b[hh] = b2 + (a4 <= (b2 ? fit1 : fit0) ? 1 : 0);
-    }
-    const Hif4Mid mid = hif4_mid(c1);
-    const float step[2] = {hif4_step(c1, b[0]), hif4_step(c1, b[1])};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t k = hif4_k(x[i], c1, b[i / 4], mid);
-      code[i] = ((__float_as_uint(x[i]) >> 28) & 8u) | k;
-      val[i] = hif4_signed_value(k, step[i / 4], x[i]);
+struct Q8 {
+  uint32_t w;      // MXFP4: the codes as nibbles, element 2i in the low nibble of byte i
+  uint32_t nb[2];  // HiF4: the codes of elements 4h .. 4h+3 in the low nibbles of nb[h]'s bytes
+  float v[8];      // MXFP4: the values; HiF4: the signed integers k (value k * step)
+  float step[2];   // HiF4: grid step of elements 4h .. 4h+3
+  uint32_t scale;  // scale byte: MXFP4 E8M0, HiF4 level-1 code
+  int b[2], b2;    // HiF4: level-2 + level-3 shift of elements 4h .. 4h+3, level-2 bit
+
+  __device__ __forceinline__ float value(int i) const { return FMT == kMX ? v[i] : v[i] * step[i / 4]; }
+  // x - value, exact in float32 for bf16 x
+  __device__ __forceinline__ float residual(int i, float x) const {
+    return FMT == kMX ? x - v[i] : fmaf(-v[i], step[i / 4], x);
+  }
+  __device__ __forceinline__ uint32_t nibbles() const {  // all eight codes as nibbles
+    if constexpr (FMT == kMX) return w;
+    return __builtin_amdgcn_perm(nb[1] | (nb[1] >> 4), nb[0] | (nb[0] >> 4), 0x06040200u);
+  }
+  // codes of pruned elements become +0: S_2:4, or elements whose bit is clear in `keep`
+  __device__ __forceinline__ void prune24() {
+    if constexpr (FMT == kMX) {
+      w = keep_2_of_4_nibbles(w);
+    } else {
+      nb[0] = keep_2_of_4_bytes(nb[0]);
+      nb[1] = keep_2_of_4_bytes(nb[1]);
     }
   }
+  template <int G>
+  __device__ __forceinline__ void prune_nm(int k) {
+    const uint32_t n = nibbles();
+    uint32_t c[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = (n >> (4 * i)) & 15u;
+    const uint32_t keep = keep_local8<G>(c, b, k);
+    if constexpr (FMT == kMX) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m |= ((keep >> i) & 1u) * (15u << (4 * i));
+      w &= m;
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m |= ((keep >> (4 * h + i)) & 1u) * (15u << (8 * i));
+        nb[h] &= m;
+      }
+    }
+  }
+};
+
+template <int FMT>
+__device__ __forceinline__ Q8<FMT> quantize8(const float x[8]) {
+  Q8<FMT> q;
+  float a4[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    a4[h] = fmaxf(fmaxf(fabsf(x[4 * h]), fabsf(x[4 * h + 1])), fmaxf(fabsf(x[4 * h + 2]), fabsf(x[4 * h + 3])));
+  const float a = fmaxf(a4[0], a4[1]);
+  if constexpr (FMT == kMX) {
+    const int E = mx_exponent(group_max<4>(a));
+    q.scale = (uint32_t)(E + 127);
+    q.b[0] = q.b[1] = 0;
+    const float sc = mx_scale_f32(E);
+    uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[0], x[1], sc, 0);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, x[2], x[3], sc, 1);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, x[4], x[5], sc, 2);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, x[6], x[7], sc, 3);
+    q.w = w;
+    const auto v0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc, 0), v1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc, 1),
+               v2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc, 2), v3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc, 3);
+    q.v[0] = v0[0]; q.v[1] = v0[1]; q.v[2] = v1[0]; q.v[3] = v1[1];
+    q.v[4] = v2[0]; q.v[5] = v2[1]; q.v[6] = v3[0]; q.v[7] = v3[1];
+  } else {
+    const int c1 = hif4_c1(group_max<8>(a));
+    q.scale = (uint32_t)c1;
+    const float inv_q = hif4_inv_q(c1), step0 = hif4_grid(c1, inv_q, 0).step;
+    q.b2 = a <= hif4_half_fit(step0) ? 1 : 0;  // this lane's 8 elements are one level-2 group
+    const float fit3 = hif4_half_fit(q.b2 ? 0.5f * step0 : step0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      q.b[h] = q.b2 + (a4[h] <= fit3 ? 1 : 0);
+      const Hif4Grid g = hif4_grid(c1, inv_q, q.b[h]);
+      q.step[h] = g.step;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) q.v[4 * h + i] = hif4_round(x[4 * h + i], g);
+      q.nb[h] = hif4_code_bytes(q.v + 4 * h, x + 4 * h);
+    }
+  }
+  return q;
 }
 
 // Threads s = 0..3 of a lane record hold its 24-byte E2M3 run as 48 bits each (r: two 24-bit
@@ -242,79 +271,148 @@ __device__ __forceinline__ void store_e2m3_run(uint8_t* __restrict__ f, int l, i
     *reinterpret_cast<uint32_t*>(s == 0 ? f + l * 16 + 4 : f + kHiTail + l * 8) = w1 | (p0 << 16);
 }
 
-__device__ __forceinline__ uint32_t codes_to_bytes(const uint32_t c[4]) {
-  return c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-}
-
 // The 4 threads of lane record `rec` (slice s = lane % 4) write it; tab: the HiF4 split table.
 template <int FMT>
 __device__ __forceinline__ void store_record8(uint8_t* __restrict__ frag, uint8_t* __restrict__ fsc,
-                                              int64_t rec, int s, const uint32_t code[8],
-                                              uint32_t scale_byte, int c1, const int b[2], const uint4* tab) {
+                                              int64_t rec, int s, const Q8<FMT>& q, const uint4* tab) {
+  uint32_t scale = q.scale;
   if constexpr (FMT == kMX) {
-    uint32_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) w |= code[i] << (4 * i);
-    reinterpret_cast<uint32_t*>(frag + rec * 16)[s] = w;
+    reinterpret_cast<uint32_t*>(frag + rec * 16)[s] = q.w;
   } else {
     uint8_t* f = frag + (rec >> 6) * kHiAFrag;
-    const int l = (int)(rec & 63), m3 = 3 * (c1 & 3);
+    const int l = (int)(rec & 63), m3 = 3 * (int)(scale & 3u);
     uint32_t rh[2], rl[2];
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) hif4_split4(codes_to_bytes(code + 4 * hh), tab[m3 + b[hh]], rh[hh], rl[hh]);
+    for (int hh = 0; hh < 2; ++hh) hif4_split4(q.nb[hh], tab[m3 + q.b[hh]], rh[hh], rl[hh]);
     store_e2m3_run(f, l, s, rh);
     reinterpret_cast<uint32_t*>(f + kHiLo + l * 16)[s] = rl[0] | (rl[1] << 16);
-    scale_byte = hif4_act_scale(scale_byte);
+    scale = hif4_act_scale(scale);
   }
-  if (s == 0) fsc[rec] = (uint8_t)scale_byte;
+  if (s == 0) fsc[rec] = (uint8_t)scale;
 }
 
-// K-major output of one thread's 8 codes (row `row`, elements 64kb + 32half + 8s .. +7) for
-// a global selection: the codes as one 32-bit word, the block's scale (MXFP4: the E8M0 byte
-// of the 32-element half; HiF4: the metadata word of the 64-block, assembled from the 8
-// lanes of the row, lane g = level-2 group g), and the exact per-scale-block sum of squares
-// of the dequantized values.  Every lane must call this (ballots, shuffles); `in` = the
-// elements lie inside the matrix.
 __device__ __forceinline__ uint32_t spread8(uint32_t x) {  // bit i -> bit 2i
   x = (x | (x << 4)) & 0x0F0Fu;
   x = (x | (x << 2)) & 0x3333u;
   return (x | (x << 1)) & 0x5555u;
 }
 
+// HiF4 metadata word of a row's 64-block, from the 8 lanes of the row (lane g = level-2 group g;
+// every lane must call this).
+__device__ __forceinline__ uint32_t hif4_meta8(uint32_t c1, const int b[2], int b2) {
+  const int base = __lane_id() & ~7;
+  const uint32_t bits2 = (uint32_t)(__ballot(b2 != 0) >> base) & 0xFFu;
+  const uint32_t b3a = (uint32_t)(__ballot(b[0] != b2) >> base) & 0xFFu;
+  const uint32_t b3b = (uint32_t)(__ballot(b[1] != b2) >> base) & 0xFFu;
+  return c1 | (bits2 << 8) | ((spread8(b3a) | (spread8(b3b) << 1)) << 16);
+}
+
+// K-major output of one thread's 8 codes (row `row`, elements 64kb + 32half + 8s .. +7) for
+// a global selection: the codes as one 32-bit word, the block's scale (MXFP4: the E8M0 byte
+// of the 32-element half; HiF4: the metadata word of the 64-block), and, where wanted, the
+// exact per-scale-block sum of squares of the dequantized values.  Every lane must call this
+// (ballots, shuffles); `in` = the elements lie inside the matrix.
 template <int FMT>
 __device__ __forceinline__ void store_kmajor8(uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                                              double* __restrict__ partials, bool in, int64_t row,
-                                              int64_t d, int64_t kb, int half, int s,
-                                              const uint32_t code[8], const float val[8],
-                                              uint32_t scale_byte, const int b[2], int b2,
-                                              double* __restrict__ rowsq = nullptr) {
+                                              bool in, int64_t row, int64_t d, int64_t kb, int half, int s,
+                                              const Q8<FMT>& q, double* __restrict__ rowsq) {
   const int64_t col0 = kb * 64 + 32 * half + 8 * s;
-  uint32_t w = 0;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) w |= code[i] << (4 * i);
-  if (in) *reinterpret_cast<uint32_t*>(codes + row * (d / 2) + col0 / 2) = w;
-  double sq = 0.0;  // exact: squares of a shared scale times small integers
-#pragma unroll
-  for (int i = 0; i < 8; ++i) sq += (double)val[i] * (double)val[i];
+  if (in) *reinterpret_cast<uint32_t*>(codes + row * (d / 2) + col0 / 2) = q.nibbles();
   if constexpr (FMT == kMX) {
-    sq = group_sum<4>(sq);
-    if (in && s == 0) {
-      scales[row * (d / 32) + kb * 2 + half] = (uint8_t)scale_byte;
-      if (partials) partials[row * (d / 32) + kb * 2 + half] = sq;
-    }
-    if (rowsq && s == 0) rowsq[half] = in ? sq : 0.0;  // this row's sum of scale block `half`
+    if (in && s == 0) scales[row * (d / 32) + kb * 2 + half] = (uint8_t)q.scale;
   } else {
-    const int base = __lane_id() & ~7;  // the row's 8 lanes
-    const uint32_t bits2 = (uint32_t)(__ballot(b2 != 0) >> base) & 0xFFu;
-    const uint32_t b3a = (uint32_t)(__ballot(b[0] != b2) >> base) & 0xFFu;
-    const uint32_t b3b = (uint32_t)(__ballot(b[1] != b2) >> base) & 0xFFu;
-    const uint32_t meta = scale_byte | (bits2 << 8) | ((spread8(b3a) | (spread8(b3b) << 1)) << 16);
-    sq = group_sum<8>(sq);
-    if (in && half == 0 && s == 0) {
-      reinterpret_cast<uint32_t*>(scales)[row * (d / 64) + kb] = meta;
-      if (partials) partials[row * (d / 64) + kb] = sq;
+    const uint32_t meta = hif4_meta8(q.scale, q.b, q.b2);
+    if (in && half == 0 && s == 0) reinterpret_cast<uint32_t*>(scales)[row * (d / 64) + kb] = meta;
+  }
+  if (rowsq == nullptr) return;  // workgroup-uniform
+  double sq = 0.0;
+  if constexpr (FMT == kMX) {
+    // exact: squares of a shared scale times small integers
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sq += (double)q.v[i] * (double)q.v[i];
+    sq = group_sum<4>(sq);
+    if (s == 0) rowsq[half] = in ? sq : 0.0;  // this row's sum of scale block `half`
+  } else {
+    // exact: the sum of four k^2 (at most 196) times step^2 (at most 12 bits)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float k2 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) k2 = fmaf(q.v[4 * h + i], q.v[4 * h + i], k2);
+      sq += (double)k2 * ((double)q.step[h] * (double)q.step[h]);
     }
-    if (rowsq && half == 0 && s == 0) rowsq[0] = in ? sq : 0.0;  // this row's sum of the 64-block
+    sq = group_sum<8>(sq);
+    if (half == 0 && s == 0) rowsq[0] = in ? sq : 0.0;  // this row's sum of the 64-block
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// Q along rows, K-major output: 8 consecutive elements per lane (an MXFP4 block is 4 lanes, a HiF4
+// block 8), 2^lx lanes along a row and 256 >> lx rows at a time, kRowsAhead such steps loaded
+// before the first is quantized.  Bound by HBM for MXFP4 and by VALU issue for HiF4.
+// ---------------------------------------------------------------------------------------
+constexpr int kRowsAhead = 4;
+
+// 8 consecutive elements; VEC: 0 single loads, 1 pieces of four elements, 2 (bf16) 16 bytes.
+template <bool F32, int VEC>
+__device__ __forceinline__ void load8(const void* x, int64_t i, float v[8]) {
+  if constexpr (VEC == 2) {
+    const uint4 t = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(x) + i);
+    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[2 * e] = bf16_to_f32(w[e] & 0xFFFFu);
+      v[2 * e + 1] = bf16_to_f32(w[e] >> 16);
+    }
+  } else {
+    load4<F32, VEC == 1>(x, i, v);
+    load4<F32, VEC == 1>(x, i + 4, v + 4);
+  }
+}
+
+template <int FMT, bool F32, int VEC>
+__global__ __launch_bounds__(kThreads) void quant_rows_kernel(const void* __restrict__ x, int64_t rows,
+                                                              int64_t cols, int64_t ld, int lx, bool codes4,
+                                                              uint8_t* __restrict__ codes,
+                                                              void* __restrict__ scales) {
+  const int tx = threadIdx.x & ((1 << lx) - 1), ty = threadIdx.x >> lx, rstep = kThreads >> lx;
+  const int64_t j8 = ((int64_t)blockIdx.x << lx) + tx;
+  if (8 * j8 >= cols) return;  // whole blocks drop out together (cols % block == 0)
+  constexpr int G = FMT == kMX ? 4 : 8;  // lanes per block
+  // this lane's offsets within a step's rows; the step's first row is uniform
+  const int64_t xoff = ty * ld + 8 * j8, coff = ty * (cols / 2) + 4 * j8, soff = ty * (cols / (8 * G)) + j8 / G;
+  for (int64_t r0 = (int64_t)blockIdx.y * rstep * kRowsAhead; r0 < rows; r0 += (int64_t)gridDim.y * rstep * kRowsAhead) {
+    float v[kRowsAhead][8];
+#pragma unroll
+    for (int u = 0; u < kRowsAhead; ++u) {
+      const int64_t row = r0 + u * rstep;
+      if (row + ty < rows) {
+        load8<F32, VEC>(x, row * ld + xoff, v[u]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[u][i] = 0.f;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsAhead; ++u) {
+      const int64_t row = r0 + u * rstep;
+      const Q8<FMT> q = quantize8<FMT>(v[u]);
+      const uint32_t meta = FMT == kMX ? q.scale : hif4_meta8(q.scale, q.b, q.b2);
+      if (row + ty >= rows) continue;
+      uint8_t* at = codes + row * (cols / 2) + coff;
+      const uint32_t w = q.nibbles();
+      if (codes4) {  // codes is 4-byte aligned (uniform)
+        *reinterpret_cast<uint32_t*>(at) = w;
+      } else {
+        reinterpret_cast<uint16_t*>(at)[0] = (uint16_t)w;
+        reinterpret_cast<uint16_t*>(at)[1] = (uint16_t)(w >> 16);
+      }
+      if ((tx & (G - 1)) == 0) {
+        const int64_t si = row * (cols / (8 * G)) + soff;
+        if constexpr (FMT == kMX) reinterpret_cast<uint8_t*>(scales)[si] = (uint8_t)meta;
+        else reinterpret_cast<uint32_t*>(scales)[si] = meta;
+      }
+    }
   }
 }
 
@@ -561,7 +659,7 @@ template <int FMT, int MODE, bool VEC, int PROD>
 __device__ __forceinline__ void residual_frag_tile(
     const uint16_t* __restrict__ X, int64_t m, int64_t d, int64_t ldx, int64_t nkb,
     uint8_t* __restrict__ fx, uint8_t* __restrict__ fsx, uint8_t* __restrict__ fr,
-    uint8_t* __restrict__ fsr, double* __restrict__ partials, int nm_keep, const Producer& prod,
+    uint8_t* __restrict__ fsr, int nm_keep, const Producer& prod,
     int64_t t, int64_t kb, uint32_t* ehist_lds, double* rowsq_lds, double* __restrict__ bkeys,
     const uint4* tab) {
   const int64_t f = t * nkb + kb;  // fragment index
@@ -593,33 +691,17 @@ __device__ __forceinline__ void residual_frag_tile(
     for (int i = 0; i < 8; ++i) x[i] = 0.f;
   }
   const int64_t rec = f * 64 + rr + 32 * half;
-  uint32_t code[8], scale_byte;
-  float val[8];
-  int c1, b[2], b2;
-  quantize8<FMT>(x, code, val, scale_byte, c1, b, b2);
-  store_record8<FMT>(fx, fsx, rec, s, code, scale_byte, c1, b, tab);
+  Q8<FMT> q = quantize8<FMT>(x);
+  store_record8<FMT>(fx, fsx, rec, s, q, tab);
   if constexpr (MODE != kResidNone) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] -= val[i];  // dX, exact in float32
-    quantize8<FMT>(x, code, val, scale_byte, c1, b, b2);
-    if constexpr (MODE == kResid24) {
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const uint32_t c4[4] = {code[4 * g], code[4 * g + 1], code[4 * g + 2], code[4 * g + 3]};
-        const uint32_t keep = keep_2_of_4(c4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (!((keep >> e) & 1u)) code[4 * g + e] = 0u;
-      }
-    } else if constexpr (MODE == kResidNM4 || MODE == kResidNM8) {
-      const uint32_t keep = keep_local8<MODE == kResidNM4 ? 4 : 8>(code, b, nm_keep);
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (!((keep >> e) & 1u)) code[e] = 0u;
-    }
+    for (int i = 0; i < 8; ++i) x[i] = q.residual(i, x[i]);  // dX, exact in float32
+    q = quantize8<FMT>(x);
+    if constexpr (MODE == kResid24) q.prune24();
+    else if constexpr (MODE == kResidNM4) q.template prune_nm<4>(nm_keep);
+    else if constexpr (MODE == kResidNM8) q.template prune_nm<8>(nm_keep);
     if constexpr (MODE == kResidDense) {
-      store_kmajor8<FMT>(fr, fsr, partials, row < m && col0 < d, row, d, kb, half, s, code, val,
-                         scale_byte, b, b2, bkeys ? rowsq_lds + 2 * rr : nullptr);
+      store_kmajor8<FMT>(fr, fsr, row < m && col0 < d, row, d, kb, half, s, q, bkeys ? rowsq_lds + 2 * rr : nullptr);
       if (bkeys) {  // workgroup-uniform
         // the key of 32 x 64 block (t, kb): its rows' scale-block sums, rows in order, scale
         // blocks in column order (the order the selection defines)
@@ -639,25 +721,24 @@ __device__ __forceinline__ void residual_frag_tile(
         // the keys its passes decode from these codes (one float32 per value)
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          hist_add_copies(ehist_lds, 256, (__float_as_uint(val[i]) >> 23) & 255u, row < m && col0 < d);
+          hist_add_copies(ehist_lds, 256, (__float_as_uint(q.value(i)) >> 23) & 255u, row < m && col0 < d);
       }
     } else {
-      store_record8<FMT>(fr, fsr, rec, s, code, scale_byte, c1, b, tab);
+      store_record8<FMT>(fr, fsr, rec, s, q, tab);
     }
   }
 }
 
 // grid: x = K step, y = row tiles (grid-stride).  kResidDense (a global selection follows):
-// fr / fsr receive the K-major Q(dX) codes and scales and `partials` its per-scale-block
-// sums of squares (may be null); with ehist (element-wise selection, cleared beforehand) the
-// workgroup also counts the exponent fields of |Q(dX)| and adds them into copy
+// fr / fsr receive the K-major Q(dX) codes and scales; with ehist (element-wise selection,
+// cleared beforehand) the workgroup also counts the exponent fields of |Q(dX)| and adds them into copy
 // (workgroup % kElemHistCopies) of that histogram; with bkeys (block selection) it writes the
 // key of each 32 x 64 block it covers (d % 64 == 0).
 template <int FMT, int MODE, bool VEC, int PROD>
 __global__ __launch_bounds__(256) void residual_frag_kernel(
     const uint16_t* __restrict__ X, int64_t m, int64_t d, int64_t ldx, int64_t nkb,
     uint8_t* __restrict__ fx, uint8_t* __restrict__ fsx, uint8_t* __restrict__ fr,
-    uint8_t* __restrict__ fsr, double* __restrict__ partials, uint32_t* __restrict__ ehist,
+    uint8_t* __restrict__ fsr, uint32_t* __restrict__ ehist,
     int nm_keep, Producer prod, double* __restrict__ bkeys) {
   __shared__ uint32_t lh[MODE == kResidDense ? kLdsCopies * 257 : 1];  // hist.h copies of 256 bins
   __shared__ double rowsq[MODE == kResidDense ? 64 : 1];  // block keys: the tile's row sums
@@ -669,7 +750,7 @@ __global__ __launch_bounds__(256) void residual_frag_kernel(
   if (FMT == kHI || counting) __syncthreads();
   const int64_t mtiles = (m + 31) / 32;
   for (int64_t t = blockIdx.y; t < mtiles; t += gridDim.y)
-    residual_frag_tile<FMT, MODE, VEC, PROD>(X, m, d, ldx, nkb, fx, fsx, fr, fsr, partials, nm_keep,
+    residual_frag_tile<FMT, MODE, VEC, PROD>(X, m, d, ldx, nkb, fx, fsx, fr, fsr, nm_keep,
                                                prod, t, blockIdx.x, counting ? lh : nullptr, rowsq,
                                                MODE == kResidDense ? bkeys : nullptr, tab);
   if (counting) {
@@ -692,13 +773,12 @@ __global__ __launch_bounds__(256) void residual_frag_kernel(
 
 // HiF4 weight-side record: the 4 threads of lane record `rec` hold 8 E2M3 fields each.
 __device__ __forceinline__ void store_record8_weight(uint8_t* __restrict__ frag, uint8_t* __restrict__ fsc,
-                                                     int64_t rec, int s, const uint32_t code[8],
-                                                     uint32_t scale_byte, const int b[2]) {
+                                                     int64_t rec, int s, const Q8<kHI>& q) {
   uint32_t r[2];  // two 24-bit runs of 4 fields
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh) r[hh] = hif4_e2m3x4(codes_to_bytes(code + 4 * hh), (uint32_t)b[hh]);
+  for (int hh = 0; hh < 2; ++hh) r[hh] = hif4_e2m3x4(q.nb[hh], (uint32_t)q.b[hh]);
   store_e2m3_run(frag + (rec >> 6) * kHiBFrag, (int)(rec & 63), s, r);
-  if (s == 0) fsc[rec] = (uint8_t)scale_byte;
+  if (s == 0) fsc[rec] = (uint8_t)q.scale;
 }
 
 // With DUAL, the same tile also yields the row quantization (blocks along the columns of x)
@@ -745,13 +825,10 @@ __device__ __forceinline__ void quant_cols_frag_tile(const uint16_t* __restrict_
     float v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = bf16_to_f32(tile[(32 * half + 8 * s + e) * kPitch + 32 * tt + rr]);
-    uint32_t code[8], scale_byte;
-    float val[8];
-    int c1, b[2], b2;
-    quantize8<FMT>(v, code, val, scale_byte, c1, b, b2);
+    const Q8<FMT> q = quantize8<FMT>(v);
     const int64_t rec = (t * nkb + kb) * 64 + rr + 32 * half;
-    if constexpr (PMODE == kPackHiB) store_record8_weight(frag, fsc, rec, s, code, scale_byte, b);
-    else store_record8<FMT>(frag, fsc, rec, s, code, scale_byte, c1, b, tab);
+    if constexpr (PMODE == kPackHiB) store_record8_weight(frag, fsc, rec, s, q);
+    else store_record8<FMT>(frag, fsc, rec, s, q, tab);
   }
   if constexpr (DUAL) {
     const int64_t rkb = (C + 63) / 64, rnt = (R + 31) / 32;  // row operand: K steps, row tiles
@@ -768,11 +845,7 @@ __device__ __forceinline__ void quant_cols_frag_tile(const uint16_t* __restrict_
         v[2 * e] = bf16_to_f32(w & 0xFFFFu);
         v[2 * e + 1] = bf16_to_f32(w >> 16);
       }
-      uint32_t code[8], scale_byte;
-      float val[8];
-      int c1, b[2], b2;
-      quantize8<FMT>(v, code, val, scale_byte, c1, b, b2);
-      store_record8<FMT>(rfrag, rfsc, (t * rkb + k) * 64 + rr + 32 * half, s, code, scale_byte, c1, b, tab);
+      store_record8<FMT>(rfrag, rfsc, (t * rkb + k) * 64 + rr + 32 * half, s, quantize8<FMT>(v), tab);
     }
   }
 }
@@ -803,17 +876,22 @@ inline unsigned grid_rows(int64_t rows) { return (unsigned)(rows < 65535 ? rows 
 void launch_quant_rows(int fmt, const void* x, bool in_f32, int64_t rows, int64_t cols,
                        int64_t ld, uint8_t* codes, void* scales, hipStream_t s) {
   if (rows == 0 || cols == 0) return;
-  const dim3 grid((unsigned)((cols / 4 + kThreads - 1) / kThreads), grid_rows(rows));
+  // lanes along a row: enough for the row up to a workgroup, at least a wave's 64
+  int lx = 6;
+  while (lx < 8 && (cols / 8) > ((int64_t)1 << lx)) ++lx;
+  const int64_t per = (int64_t)(kThreads >> lx) * kRowsAhead;
+  const dim3 grid((unsigned)((cols / 8 + ((int64_t)1 << lx) - 1) >> lx), grid_rows((rows + per - 1) / per));
   const size_t esz = in_f32 ? 4 : 2;
-  const bool vec = ((uintptr_t)x % (4 * esz) == 0) && (ld % 4 == 0);
-#define RESQ_QR(F, I, V) hipLaunchKernelGGL((quant_rows_kernel<F, I, V>), grid, dim3(kThreads), 0, s, x, rows, cols, ld, codes, scales)
-  if (fmt == kMX) {
-    if (in_f32) { if (vec) RESQ_QR(kMX, true, true); else RESQ_QR(kMX, true, false); }
-    else { if (vec) RESQ_QR(kMX, false, true); else RESQ_QR(kMX, false, false); }
-  } else {
-    if (in_f32) { if (vec) RESQ_QR(kHI, true, true); else RESQ_QR(kHI, true, false); }
-    else { if (vec) RESQ_QR(kHI, false, true); else RESQ_QR(kHI, false, false); }
-  }
+  const bool vec4 = (uintptr_t)x % (4 * esz) == 0 && ld % 4 == 0, vec8 = (uintptr_t)x % 16 == 0 && ld % 8 == 0;
+  const bool codes4 = (uintptr_t)codes % 4 == 0;
+#define RESQ_QR(F, I, V) hipLaunchKernelGGL((quant_rows_kernel<F, I, V>), grid, dim3(kThreads), 0, s, x, rows, cols, ld, lx, codes4, codes, scales)
+#define RESQ_QR_VEC(F)                                                          \
+  if (in_f32) { if (vec4) RESQ_QR(F, true, 1); else RESQ_QR(F, true, 0); }      \
+  else if (vec8) RESQ_QR(F, false, 2);                                          \
+  else if (vec4) RESQ_QR(F, false, 1);                                          \
+  else RESQ_QR(F, false, 0);
+  if (fmt == kMX) { RESQ_QR_VEC(kMX) } else { RESQ_QR_VEC(kHI) }
+#undef RESQ_QR_VEC
 #undef RESQ_QR
 }
 
@@ -870,7 +948,7 @@ void launch_residual(int fmt, int mode, const uint16_t* X, int64_t m, int64_t d,
     const bool vec16 = prod ? ((uintptr_t)pr.g % 16 == 0 && (uintptr_t)pr.u % 16 == 0 &&
                                pr.ldg % ve == 0 && pr.ldu % ve == 0)
                             : ((uintptr_t)X % 16 == 0 && ldx % 8 == 0);
-#define RESQ_RF(F, M, V, P) launch_timed(residual_frag_kernel<F, M, V, P>, grid, dim3(256), 0u, s, X, m, d, ldx, nkb, qx_codes, (uint8_t*)qx_scales, qr_codes, (uint8_t*)qr_scales, partials, ehist, nm_keep, pr, bkeys)
+#define RESQ_RF(F, M, V, P) launch_timed(residual_frag_kernel<F, M, V, P>, grid, dim3(256), 0u, s, X, m, d, ldx, nkb, qx_codes, (uint8_t*)qx_scales, qr_codes, (uint8_t*)qr_scales, ehist, nm_keep, pr, bkeys)
 #define RESQ_RF_MODE(F, V, P)                                        \
     switch (mode) {                                                  \
       case kResidNone: RESQ_RF(F, kResidNone, V, P); break;          \

@@ -41,9 +41,11 @@ __device__ __forceinline__ Quad quantize_quad(const float x[4]) {
   } else {
     const float A = group_max<16>(a);
     q.c1 = hif4_c1(A);
+    const float inv_q = hif4_inv_q(q.c1);
     const float ag = max_mag(a, __uint_as_float(dpp_u32<kDppXor1>(__float_as_uint(a))));
-    const int b2 = ag <= hif4_half_fit(q.c1, 0) ? 1 : 0;
-    const int b3 = a <= hif4_half_fit(q.c1, b2) ? 1 : 0;
+    const float step0 = hif4_grid(q.c1, inv_q, 0).step;
+    const int b2 = ag <= hif4_half_fit(step0) ? 1 : 0;
+    const int b3 = a <= hif4_half_fit(b2 ? 0.5f * step0 : step0) ? 1 : 0;
     q.b = b2 + b3;
     q.E = 0;
     const int lane = __lane_id();
@@ -53,13 +55,12 @@ __device__ __forceinline__ Quad quantize_quad(const float x[4]) {
     const uint32_t bits3 = (uint32_t)(m3 >> base) & 0xFFFFu;
     const uint32_t bits2 = even_bits16((uint32_t)(m2 >> base) & 0xFFFFu);
     q.scale = (uint32_t)q.c1 | (bits2 << 8) | (bits3 << 16);
-    const Hif4Mid mid = hif4_mid(q.c1);
-    const float step = hif4_step(q.c1, q.b);
+    const Hif4Grid g = hif4_grid(q.c1, inv_q, q.b);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t k = hif4_k(x[i], q.c1, q.b, mid);
-      q.code[i] = ((__float_as_uint(x[i]) >> 28) & 8u) | k;
-      q.val[i] = hif4_signed_value(k, step, x[i]);
+      const float k = hif4_round(x[i], g);
+      q.code[i] = ((__float_as_uint(x[i]) >> 28) & 8u) | (uint32_t)fabsf(k);
+      q.val[i] = k * g.step;
     }
   }
   return q;
@@ -84,6 +85,29 @@ __device__ __forceinline__ uint32_t keep_2_of_4(const uint32_t c[4]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) keep |= (k[i] >= second ? 1u : 0u) << i;
   return keep;
+}
+
+// S_2:4 on four codes, one per byte: the kept codes, the others zeroed.  Byte keys as above;
+// (key | 0x80) - other keeps bit 7 where key > other, and an element is kept when it beats two
+// of the other three.
+__device__ __forceinline__ uint32_t keep_2_of_4_bytes(uint32_t nb) {
+  const uint32_t key = ((nb & 0x07070707u) << 2) | 0x00010203u, hi = key | 0x80808080u;
+  const uint32_t d1 = hi - __builtin_amdgcn_alignbyte(key, key, 1), d2 = hi - __builtin_amdgcn_alignbyte(key, key, 2),
+                 d3 = hi - __builtin_amdgcn_alignbyte(key, key, 3);
+  const uint32_t two = ((d1 & d2) | (d1 & d3) | (d2 & d3)) & 0x80808080u;
+  return nb & (two | (two - (two >> 7)));
+}
+// The same on eight codes as nibbles of w (element 2i in the low nibble of byte i): even
+// elements e and odd elements o as bytes, each group's partners in the neighbouring byte.
+__device__ __forceinline__ uint32_t keep_2_of_4_nibbles(uint32_t w) {
+  const uint32_t e = ((w & 0x07070707u) << 2) | 0x01030103u, o = ((w >> 2) & 0x1C1C1C1Cu) | 0x00020002u;
+  const uint32_t es = __builtin_amdgcn_perm(e, e, 0x02030001u), os = __builtin_amdgcn_perm(o, o, 0x02030001u);
+  const uint32_t eh = e | 0x80808080u, oh = o | 0x80808080u;
+  const uint32_t e1 = eh - o, e2 = eh - os, e3 = eh - es, o1 = oh - e, o2 = oh - es, o3 = oh - os;
+  const uint32_t ke = (((e1 & e2) | (e1 & e3) | (e2 & e3)) >> 7) & 0x01010101u;
+  const uint32_t ko = (((o1 & o2) | (o1 & o3) | (o2 & o3)) >> 7) & 0x01010101u;
+  const uint32_t me = (ke << 4) - ke, mo = (ko << 4) - ko;  // 0x0F in kept bytes
+  return w & (me | (mo << 4));
 }
 
 // S_k:g on one group of G (4 or 8) consecutive elements given as magnitudes on one common
