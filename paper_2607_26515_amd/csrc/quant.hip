@@ -530,6 +530,12 @@ __device__ float sqrt_rn_f32(float t) {
   return z;
 }
 
+// The row's sum of squares s is the exact sum rounded once to float32.  It is first added in
+// float64, where every square is exact and the positive terms' sum S is off by at most a
+// relative (terms per lane + tree depth) 2^-53: where S (1 - e) and S (1 + e) round to the same
+// float32 for a bound e above that, so does the exact sum.  Otherwise (S next to a float32 midpoint,
+// about one row in 2^22 at d = 2048) the exact integer sum below decides.
+//
 // A bf16 value is M * 2^(E - 134) with M < 2^8 (E = the exponent field, 1 for subnormals), so
 // its square is M^2 * 2^(2E - 268).  One row's squares are added as integers per exponent
 // field (LDS histograms in kLdsCopies per-lane copies, hist.h; a copy's bin gets at most
@@ -541,7 +547,7 @@ __device__ float sqrt_rn_f32(float t) {
 // (53 >= 24 + 2 bits).
 constexpr int kRmsLimbs = 18;
 
-__device__ float rms_row_factor(const unsigned long long* limb, int64_t d, float eps) {
+__device__ float exact_square_sum(const unsigned long long* limb) {
   uint32_t n[kRmsLimbs];
   unsigned long long carry = 0;
 #pragma unroll
@@ -571,58 +577,115 @@ __device__ float rms_row_factor(const unsigned long long* limb, int64_t d, float
     if (sticky) sig |= 1ull;
     s = (float)ldexp((double)sig, msb - 52 - 268);  // exact in float64, then one rounding
   }
+  return s;
+}
+
+__device__ float rms_row_factor(float s, int64_t d, float eps) {
   const float mu = div_rn_f32(s, (float)d);
   const float t = mu + eps;
   return div_rn_f32(1.f, sqrt_rn_f32(t));
 }
 
-// grid-stride over rows, one workgroup of 256 threads per row at a time
+// 8 bf16 patterns of a row from element c.
 template <bool VEC>
+__device__ __forceinline__ void load_bits8(const uint16_t* __restrict__ src, int64_t c, uint32_t b[8]) {
+  if constexpr (VEC) {
+    const uint4 u = *reinterpret_cast<const uint4*>(src + c);
+    const uint32_t v[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { b[2 * e] = v[e] & 0xFFFFu; b[2 * e + 1] = v[e] >> 16; }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = src[c + i];
+  }
+}
+
+// The exact sum for one row, by the whole workgroup (wh, limb: LDS); thread 0 holds the result.
+template <bool VEC>
+__device__ float exact_row_sum(const uint16_t* __restrict__ src, int64_t d, uint32_t* wh, unsigned long long* limb) {
+  const int tid = threadIdx.x;
+  uint32_t* hc = wh + (tid % kLdsCopies) * 257;  // this lane's copy
+  __syncthreads();  // an earlier row may still read the histograms and limbs
+  for (int i = tid; i < kLdsCopies * 257; i += 256) wh[i] = 0u;
+  if (tid < kRmsLimbs) limb[tid] = 0ull;
+  __syncthreads();
+  for (int64_t c = (int64_t)tid * 8; c < d; c += 256 * 8) {  // d % 8 == 0
+    uint32_t b[8];
+    load_bits8<VEC>(src, c, b);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t e = (b[i] >> 7) & 0xFFu;
+      const uint32_t mant = (b[i] & 0x7Fu) | (e ? 0x80u : 0u);
+      if (mant) atomicAdd(&hc[e ? e : 1u], mant * mant);
+    }
+  }
+  __syncthreads();
+  // bin tid (0 .. 255) at bit 2 * tid: three 32-bit pieces into three limbs
+  unsigned long long T = 0;  // up to 2^18 squares below 2^16: 64-bit
+#pragma unroll
+  for (int c = 0; c < kLdsCopies; ++c) T += wh[c * 257 + tid];
+  if (T) {
+    const int off = 2 * tid, L = off >> 5, sh = off & 31;
+    const unsigned long long lo = (T & 0xFFFFFFFFull) << sh, hi = (T >> 32) << sh;
+    atomicAdd(&limb[L], lo & 0xFFFFFFFFull);
+    atomicAdd(&limb[L + 1], (lo >> 32) + (hi & 0xFFFFFFFFull));
+    if (hi >> 32) atomicAdd(&limb[L + 2], hi >> 32);
+  }
+  __syncthreads();
+  return tid == 0 ? exact_square_sum(limb) : 0.f;
+}
+
+// One workgroup of four waves per 4 / WPR rows at a time (grid-stride), WPR waves per row: one
+// for many rows (no barrier on the way), four for few (the row's loads spread over more lanes).
+// Bound by the LDS atomics and barriers of the integer histogram when every row took it: 17.1 us
+// at m = 3001, d = 2048, 5.6 us at m = 8; now a read of H (the forward of four linears at
+// m = 3001, MXFP4, went from 388 to 369 us, with two such passes).
+template <bool VEC, int WPR>
 __global__ __launch_bounds__(256) void rms_rows_kernel(const uint16_t* __restrict__ H, int64_t m,
                                                         int64_t d, int64_t ldh, float eps,
                                                         float* __restrict__ rinv) {
+  constexpr int R = 4 / WPR;  // rows per workgroup step
   __shared__ uint32_t wh[kLdsCopies * 257];
   __shared__ unsigned long long limb[kRmsLimbs];
-  const int tid = threadIdx.x;
-  uint32_t* hc = wh + (tid % kLdsCopies) * 257;  // this lane's copy
-  for (int64_t row = blockIdx.x; row < m; row += gridDim.x) {
-    for (int i = tid; i < kLdsCopies * 257; i += 256) wh[i] = 0u;
-    if (tid < kRmsLimbs) limb[tid] = 0ull;
-    __syncthreads();
-    const uint16_t* src = H + row * ldh;
-    for (int64_t c = (int64_t)tid * 8; c < d; c += 256 * 8) {  // d % 8 == 0
-      uint32_t b[8];
-      if constexpr (VEC) {
-        const uint4 u = *reinterpret_cast<const uint4*>(src + c);
-        const uint32_t v[4] = {u.x, u.y, u.z, u.w};
+  __shared__ double part[4];
+  __shared__ int unsure[R];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = wave / WPR, t = tid - r * (64 * WPR);  // row of the step, thread within the row
+  const double bound = ((double)(d / (64 * WPR)) + 16.0) * 0x1p-52;  // twice the sum's relative error
+  for (int64_t base = (int64_t)blockIdx.x * R; base < m; base += (int64_t)gridDim.x * R) {
+    const int64_t row = base + r;
+    double acc = 0.0;
+    if (row < m) {
+      const uint16_t* src = H + row * ldh;
+      for (int64_t c = (int64_t)t * 8; c < d; c += 64 * WPR * 8) {  // d % 8 == 0
+        uint32_t b[8];
+        load_bits8<VEC>(src, c, b);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { b[2 * e] = v[e] & 0xFFFFu; b[2 * e + 1] = v[e] >> 16; }
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) b[i] = src[c + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint32_t e = (b[i] >> 7) & 0xFFu;
-        const uint32_t mant = (b[i] & 0x7Fu) | (e ? 0x80u : 0u);
-        if (mant) atomicAdd(&hc[e ? e : 1u], mant * mant);
+        for (int i = 0; i < 8; ++i) {
+          const double v = (double)bf16_to_f32(b[i]);
+          acc = fma(v, v, acc);
+        }
       }
     }
-    __syncthreads();
-    // bin tid (0 .. 255) at bit 2 * tid: three 32-bit pieces into three limbs
-    unsigned long long T = 0;  // up to 2^18 squares below 2^16: 64-bit
-#pragma unroll
-    for (int c = 0; c < kLdsCopies; ++c) T += wh[c * 257 + tid];
-    if (T) {
-      const int off = 2 * tid, L = off >> 5, sh = off & 31;
-      const unsigned long long lo = (T & 0xFFFFFFFFull) << sh, hi = (T >> 32) << sh;
-      atomicAdd(&limb[L], lo & 0xFFFFFFFFull);
-      atomicAdd(&limb[L + 1], (lo >> 32) + (hi & 0xFFFFFFFFull));
-      if (hi >> 32) atomicAdd(&limb[L + 2], hi >> 32);
+    acc = group_sum<64>(acc);
+    if constexpr (WPR > 1) {
+      if (lane == 0) part[wave] = acc;
+      __syncthreads();
+      acc = part[0] + part[1] + part[2] + part[3];
+    }
+    const float lo = (float)(acc * (1.0 - bound)), hi = (float)(acc * (1.0 + bound));
+    if (t == 0) {
+      unsure[r] = row < m && lo != hi;
+      if (row < m && lo == hi) rinv[row] = rms_row_factor(lo, d, eps);
     }
     __syncthreads();
-    if (tid == 0) rinv[row] = rms_row_factor(limb, d, eps);
-    __syncthreads();  // the next row clears the histograms and limbs
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (unsure[u]) {  // workgroup-uniform
+        const float s = exact_row_sum<VEC>(H + (base + u) * ldh, d, wh, limb);
+        if (tid == 0) rinv[base + u] = rms_row_factor(s, d, eps);
+      }
+    __syncthreads();  // the next step overwrites part and unsure
   }
 }
 
@@ -927,11 +990,15 @@ void launch_quant_cols(int fmt, const void* x, bool in_f32, int64_t rows, int64_
 void launch_rms_rows(const uint16_t* H, int64_t m, int64_t d, int64_t ldh, float eps, float* rinv,
                      hipStream_t s) {
   if (m == 0) return;
-  const unsigned grid = (unsigned)(m < 8192 ? m : 8192);
-  if ((uintptr_t)H % 16 == 0 && ldh % 8 == 0)
-    launch_timed(rms_rows_kernel<true>, dim3(grid), dim3(256), 0u, s, H, m, d, ldh, eps, rinv);
-  else
-    launch_timed(rms_rows_kernel<false>, dim3(grid), dim3(256), 0u, s, H, m, d, ldh, eps, rinv);
+  // a wave per row once that gives every CU a workgroup's worth of rows and a row is a few loads
+  const bool many = m >= 2048 && d <= 8192;
+  const int64_t groups = many ? (m + 3) / 4 : m;
+  const dim3 grid((unsigned)(groups < 8192 ? groups : 8192));
+  const bool vec = (uintptr_t)H % 16 == 0 && ldh % 8 == 0;
+#define RESQ_RMS(V, W) launch_timed(rms_rows_kernel<V, W>, grid, dim3(256), 0u, s, H, m, d, ldh, eps, rinv)
+  if (many) { if (vec) RESQ_RMS(true, 1); else RESQ_RMS(false, 1); }
+  else { if (vec) RESQ_RMS(true, 4); else RESQ_RMS(false, 4); }
+#undef RESQ_RMS
 }
 
 void launch_residual(int fmt, int mode, const uint16_t* X, int64_t m, int64_t d, int64_t ldx,

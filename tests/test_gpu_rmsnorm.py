@@ -139,3 +139,29 @@ def test_rmsnorm_largest_d():
     for fmt in FMTS:
         y, y_ref, _ = _run(h, gamma, 1e-6, fmt, "2:4", n, wb)
         assert np.array_equal(y.view(np.uint32), y_ref.view(np.uint32)), fmt
+
+
+@pytest.mark.parametrize("m,layout", [(5, "plain"), (2047, "plain"), (2048, "strided"),
+                                      (2051, "plain")])
+def test_rmsnorm_rows_at_float32_midpoints(m, layout):
+    """The float64 sum cannot decide a row whose sum of squares is at, or a 2^-120 beside, a
+    float32 midpoint: those rows take the exact integer sum.  Runs of such rows, alone and side
+    by side with ordinary ones, for one row per workgroup (m < 2048) and four, the last group
+    ragged, over both load widths; Y bit for bit as from the oracle's X."""
+    rng = np.random.default_rng(m)
+    d, n = 640, 32
+    rows = rng.standard_t(3, (m, d)).astype(np.float32)
+    odd = rng.random(m) < 0.4
+    odd[-1] = True
+    for i in np.flatnonzero(odd):
+        p = rng.permutation(d)
+        rows[i] = 0.0
+        rows[i, p[0]], rows[i, p[1]] = 1.0, -(2.0**-12)
+        if rng.random() < 0.7:
+            rows[i, p[2]] = 2.0**-60
+    h = f32_to_bf16_bits(rows)
+    gamma = _gamma(d, 3)
+    wb = weights(rng_tree(5, 1)[0], n, d)
+    for fmt in FMTS:
+        y, y_ref, _ = _run(h, gamma, 1e-6, fmt, "2:4", n, wb, layout)
+        assert np.array_equal(y.view(np.uint32), y_ref.view(np.uint32)), fmt
