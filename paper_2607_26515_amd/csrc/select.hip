@@ -37,6 +37,30 @@ __device__ __forceinline__ void mx_word_keys(uint32_t cw, uint32_t scale, uint32
   }
 }
 
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// HiF4 keys of word Q of a scale word's codes (elements 8Q .. 8Q + 7, one level-2 group and two
+// level-3 groups): value k (4 + m) 2^(e - 35 - b).  The eight magnitudes k spread to the bytes
+// of two dwords, one 16-bit-lane multiply by 4 + m forms four products k (4 + m) <= 49 at once
+// (no carry crosses a byte), each byte converts to float32 exactly, and ldexp applies the
+// group's 2^(e - 35 - b) (exact: the smallest nonzero value, 4 * 2^-37, is normal).  f2 holds
+// 4 + m in both 16-bit lanes, e35 = e - 35; l2 and l3 are the level-2 and level-3 shift bits from
+// word 0's group on.
+__device__ __forceinline__ void hif4_word_keys(uint32_t cw, uint32_t f2, int e35, uint32_t l2, uint32_t l3,
+                                               int Q, uint32_t key[8]) {
+  const uint32_t ta = __builtin_amdgcn_perm(cw, cw, 0x0C010C00u), tb = __builtin_amdgcn_perm(cw, cw, 0x0C030C02u);
+  const uint32_t ka = (ta | (ta << 4)) & 0x07070707u, kb = (tb | (tb << 4)) & 0x07070707u;
+  const uint32_t pa = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, ka) * __builtin_bit_cast(u16x2, f2));
+  const uint32_t pb = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, kb) * __builtin_bit_cast(u16x2, f2));
+  const int b2 = (int)((l2 >> Q) & 1u);
+  const int ea = e35 - b2 - (int)((l3 >> (2 * Q)) & 1u), eb = e35 - b2 - (int)((l3 >> (2 * Q + 1)) & 1u);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    key[i] = __float_as_uint(ldexpf((float)((pa >> (8 * i)) & 0xFFu), ea));
+    key[4 + i] = __float_as_uint(ldexpf((float)((pb >> (8 * i)) & 0xFFu), eb));
+  }
+}
+
 // Scale word of element (row, j): MX E8M0 byte or the HiF4 meta word.
 template <int FMT>
 __device__ __forceinline__ uint32_t scale_at(const void* scales, int64_t row, int64_t d, int64_t j) {
@@ -44,19 +68,66 @@ __device__ __forceinline__ uint32_t scale_at(const void* scales, int64_t row, in
   else return reinterpret_cast<const uint32_t*>(scales)[row * (d / 64) + j / 64];
 }
 
+// Wave scans and reductions through DPP (row shifts, then row 15 -> row broadcasts): a step is one
+// vector instruction, where a shuffle is an LDS round trip.
+// Lanes that a step gives no source take `none`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_take(uint32_t none, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)x, CTRL, ROWS, 0xF, false);
+}
+// Inclusive combination over the lanes up to this one: of its row of 16, or of the wave.
+template <typename Op>
+__device__ __forceinline__ uint32_t row_scan(uint32_t x, uint32_t none, Op op) {
+  x = op(x, dpp_take<0x111, 0xF>(none, x));
+  x = op(x, dpp_take<0x112, 0xF>(none, x));
+  x = op(x, dpp_take<0x114, 0xF>(none, x));
+  return op(x, dpp_take<0x118, 0xF>(none, x));
+}
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t none, Op op) {
+  x = row_scan(x, none, op);
+  x = op(x, dpp_take<0x142, 0xA>(none, x));
+  return op(x, dpp_take<0x143, 0xC>(none, x));
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+
+// a + b of the lanes N apart, in halves: lanes with (lane & N) == 0 get a's sum, the others b's.
+template <int N>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  uint32_t p[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t u = (uint32_t)(x >> (32 * h)), v = (uint32_t)(y >> (32 * h));
+    if constexpr (N == 32) {
+      const auto r = __builtin_amdgcn_permlane32_swap(u, v, false, false);
+      p[0][h] = r[0]; p[1][h] = r[1];
+    } else {
+      const auto r = __builtin_amdgcn_permlane16_swap(u, v, false, false);
+      p[0][h] = r[0]; p[1][h] = r[1];
+    }
+  }
+  return __longlong_as_double((long long)((uint64_t)p[0][1] << 32 | p[0][0])) +
+         __longlong_as_double((long long)((uint64_t)p[1][1] << 32 | p[1][0]));
+}
+
 // ---------------------------------------------------------------------------------------
-// Channel keys.  Workgroup = 16 channels x 64 row chunks: lane l of wave w sums the squares of
-// channel l % 16 over row chunk 4w + l / 16 in float64, and the chunk sums are added in chunk
-// (row) order.  16 channels per workgroup give d / 16 workgroups, enough to cover the CUs at
-// the layer widths of a decode batch.  The result equals the defined row-by-row sum exactly
-// whenever no float64 addition of either order rounds: every square v^2 is a multiple of 2^L,
-// L = twice the exponent of the lowest set bit of the smallest such v in the channel, so if
-// the total is below 2^(L+53) every partial sum, in any order, is a multiple of 2^L below
-// 2^(L+53) and thus exact.  The check uses 2^(L+52) to absorb any rounding of the computed
-// total; a channel that fails it is summed again row by row in the defined order.
+// Channel keys.  Workgroup = 64 channels x all rows: a lane takes the 8 channels of one code word
+// (4 bytes) in every 128th row, so that a wave's load is 8 rows of 32 consecutive bytes; 8 lanes'
+// sums are combined in the wave, 16 waves' through LDS.  The result equals the defined row-by-row
+// sum exactly whenever no float64 addition of either order rounds: every square v^2 is a multiple
+// of 2^L, L = twice the exponent of the smallest step that a scale word of the channel's nonzero
+// code words allows (MXFP4: half the scale; HiF4: a level-1 step of e - 37), so if the total is
+// below 2^(L+53) every partial sum, in any order, is a multiple of 2^L below 2^(L+53) and thus
+// exact.  The check uses 2^(L+52) to absorb any rounding of the computed total; a channel that
+// fails it is summed again row by row in the defined order.
+// One channel per lane (8-byte row pieces, a decode and a lowest-bit search per element) took
+// 22.7 us at m = 512, d = 18944 and 6.0 us at d = 3584, MXFP4; this way 7.4 us and 4.8 us.
 // ---------------------------------------------------------------------------------------
 constexpr int kChanThreads = 1024;  // 16 waves
-constexpr int kChanPerWg = 16;      // channels per workgroup
+constexpr int kChanPerWg = 64;      // channels per workgroup
 constexpr int kNoBit = 1 << 20;      // "no nonzero term yet" for the lowest-bit exponent
 
 template <int FMT>
@@ -73,59 +144,84 @@ __device__ __forceinline__ float decode_at(uint32_t cbyte, uint32_t sc, int64_t 
   }
 }
 
-// Exponent of the lowest set bit of a nonzero float32 (subnormals included).
-__device__ __forceinline__ int lowest_bit_exp(float v) {
-  const uint32_t u = __float_as_uint(v) & 0x7FFFFFFFu;
-  const int ef = (int)(u >> 23);
-  const uint32_t sig = ef ? ((u & 0x7FFFFFu) | 0x800000u) : u;
-  return (ef ? ef - 150 : -149) + __builtin_ctz(sig);
-}
-
 template <int FMT>
 __global__ __launch_bounds__(kChanThreads) void channel_keys_kernel(const uint8_t* __restrict__ codes,
                                                                     const void* __restrict__ scales,
                                                                     int64_t m, int64_t d,
                                                                     double* __restrict__ keys) {
-  constexpr int NW = kChanThreads / 64, NC = NW * (64 / kChanPerWg), U = 8;
-  __shared__ double part[NC][kChanPerWg];
-  __shared__ int low[NC][kChanPerWg];
+  constexpr int NW = kChanThreads / 64, WPR = kChanPerWg / 8, RW = 64 / WPR, RS = NW * RW, U = 4;
+  __shared__ double part[NW][kChanPerWg];
+  __shared__ int low[NW][WPR];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c = lane % kChanPerWg, chunk = wave * (64 / kChanPerWg) + lane / kChanPerWg;
-  const int64_t j = (int64_t)blockIdx.x * kChanPerWg + c;
-  const int64_t per = (m + NC - 1) / NC;
-  const int64_t r0 = min((int64_t)chunk * per, m), r1 = min(r0 + per, m);
-  auto value = [&](int64_t row) {
-    return decode_at<FMT>(codes[row * (d / 2) + j / 2], scale_at<FMT>(scales, row, d, j), j);
-  };
-  double acc = 0.0;
-  int lo = kNoBit;
-  if (j < d) {
-    for (int64_t r = r0; r < r1; r += U) {
-      float v[U];
+  const int cq = lane % WPR;  // code word within the workgroup's 64 channels
+  const int64_t j0 = (int64_t)blockIdx.x * kChanPerWg + 8 * cq;
+  double acc[8];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = r + u < r1 ? value(r + u) : 0.f;  // loads issued together
+  for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+  int lo = kNoBit;
+  if (j0 < d) {  // d % 8 == 0
+    for (int64_t r = wave * RW + lane / WPR; r < m; r += RS * U) {
+      uint32_t cw[U], sc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // loads issued together
+        const int64_t row = r + u * RS;
+        cw[u] = row < m ? *reinterpret_cast<const uint32_t*>(codes + row * (d / 2) + j0 / 2) : 0u;
+        sc[u] = row < m ? scale_at<FMT>(scales, row, d, j0) : 0u;
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        acc += (double)v[u] * (double)v[u];  // exact square: at most 6 significant bits in v
-        if (v[u] != 0.f) lo = min(lo, 2 * lowest_bit_exp(v[u]));
+        uint32_t key[8];
+        int step;
+        if constexpr (FMT == 0) {
+          mx_word_keys(cw[u], sc[u], key);
+          step = (int)sc[u] - 128;
+        } else {
+          const int e = (int)((sc[u] >> 2) & 63u);
+          hif4_word_keys(cw[u], (4u + (sc[u] & 3u)) * 0x00010001u, e - 35, sc[u] >> 8, sc[u] >> 16, cq, key);
+          step = e - 37;
+        }
+        if (cw[u] & 0x77777777u) lo = min(lo, 2 * step);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const double v = (double)__uint_as_float(key[e]);
+          acc[e] = fma(v, v, acc[e]);  // exact square: at most 6 significant bits in v
+        }
       }
     }
   }
-  part[chunk][c] = acc;
-  low[chunk][c] = lo;
+  // the wave's RW = 8 row lanes of each code word: halving exchanges leave one channel in each
+  // lane (lane halves, then odd and even rows of 16 lanes swap in registers; then 8 lanes on)
+  static_assert(RW == 8, "three halving exchanges");
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] = swap_add<32>(acc[e], acc[e + 4]);
+#pragma unroll
+  for (int e = 0; e < 2; ++e) acc[e] = swap_add<16>(acc[e], acc[e + 2]);
+  const bool up = (lane & 8) != 0;
+  const uint64_t send = (uint64_t)__double_as_longlong(up ? acc[0] : acc[1]);
+  const uint64_t got = (uint64_t)dpp_take<0x128, 0xF>(0u, (uint32_t)(send >> 32)) << 32 |
+                       dpp_take<0x128, 0xF>(0u, (uint32_t)send);  // rotated by 8 within 16 lanes
+  acc[0] = (up ? acc[1] : acc[0]) + __longlong_as_double((long long)got);
+  const int ch = 8 * cq + ((lane & 32) ? 4 : 0) + ((lane & 16) ? 2 : 0) + (up ? 1 : 0);
+  lo = min(lo, (int)dpp_take<0x128, 0xF>(0u, (uint32_t)lo));
+  lo = min(lo, __shfl_xor(lo, 16, 64));
+  lo = min(lo, __shfl_xor(lo, 32, 64));
+  part[wave][ch] = acc[0];
+  if (lane < WPR) low[wave][lane] = lo;
   __syncthreads();
+  const int64_t j = (int64_t)blockIdx.x * kChanPerWg + threadIdx.x;
   if (threadIdx.x >= kChanPerWg || j >= d) return;  // thread c finishes channel c
   double sum = 0.0;
   lo = kNoBit;
-  for (int w = 0; w < NC; ++w) {
-    sum += part[w][c];
-    lo = min(lo, low[w][c]);
+#pragma unroll 4
+  for (int w = 0; w < NW; ++w) {
+    sum += part[w][threadIdx.x];
+    lo = min(lo, low[w][threadIdx.x / 8]);
   }
   if (sum != 0.0 && !(sum < ldexp(1.0, lo + 52))) {
     // some addition may round: the defined order, rows 0 .. m-1
     sum = 0.0;
     for (int64_t r = 0; r < m; ++r) {
-      const float v = value(r);
+      const float v = decode_at<FMT>(codes[r * (d / 2) + j / 2], scale_at<FMT>(scales, r, d, j), j);
       sum += (double)v * (double)v;
     }
   }
@@ -213,230 +309,283 @@ __device__ __forceinline__ void choose_digit(const uint32_t* hist, int nb, uint3
   __syncthreads();
 }
 
-// Radix digit choice by one wave over a 256-bin histogram (hist.h copies, summed here): the
-// digit holding the k-th largest key (k >= 1; k = 0 picks the top digit), k's rank among the
-// keys with that digit, and that digit's count, to out[0..2].  Lane l holds bins 255 - 4l ..
-// 252 - 4l.
-__device__ __forceinline__ void choose_digit_wave(const uint32_t* hist, uint32_t k, uint32_t* out) {
-  const int lane = threadIdx.x & 63;
-  uint32_t v[4], sum = 0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    v[e] = hist_sum_copies(hist, 256, 255 - 4 * lane - e);
-    sum += v[e];
-  }
-  uint32_t incl = sum;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  uint32_t above = incl - sum;  // keys in higher bins
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if ((above < k && k <= above + v[e]) || (k == 0 && lane == 0 && e == 0)) {
-      out[0] = (uint32_t)(255 - 4 * lane - e);
-      out[1] = k - above;
-      out[2] = v[e];
-    }
-    above += v[e];
-  }
-}
-
-
 // ---------------------------------------------------------------------------------------
 // Single-workgroup top-k over n float64 keys -> bit mask (bit b of byte i = item 8i + b).
-// Thread t holds keys t, t + 1024, ... in registers (KPT of them: n <= 1024 KPT), loaded once
-// with coalesced loads.  The threshold's ties are ranked in index order from a table of
-// per-slot, per-wave tie counts that one wave scans.
+// Thread t owns keys t, t + 1024, ...  Their upper 32 bits below the sign, t = key >> 31, lie in
+// LDS as t' = t less the smallest nonzero t (plus one; 0 stays 0): the same order, and the
+// first digit starts at the highest bit in which they differ.  Digit passes of 10 bits narrow
+// the threshold; once the keys sharing its digits fit one per thread, their whole bit patterns are
+// fetched, one per thread, and once they fit one wave they are ranked directly.  Only where
+// more than 1024 keys agree in all of t' do passes over the whole keys (from global memory) follow.  The
+// threshold's ties are ranked in index order from a table of per-slot, per-wave tie counts
+// that one wave scans, unless all of them are kept.
+//
+// What bounds it is one workgroup's latency: barriers, LDS round trips and, on a kernel that runs
+// each instruction only a few times, fetching its code.  So the loops over a thread's keys stay
+// rolled, which is why the keys lie in LDS; with up to 20 keys per thread in registers (every loop
+// unrolled, 21 KB of code) and 8-bit digits at byte positions, 18944 keys took 22.0 us and
+// 3584 keys 9.7 us, now 15.1 to 17.0 us and 7.4 to 8.5 us.
 // ---------------------------------------------------------------------------------------
-// launch_top takes the smallest instantiation that holds the keys, so that a pass over a few
-// thousand keys is not a walk over many mostly empty slots.
-constexpr int kKeysPerThread = 20;  // the largest: n <= 20480 (channels of d <= 20480)
+constexpr int kMaxTopKeys = 20480;  // t' in LDS: 80 KB
 
-// BP = 0: the keys are read from `keys`; BP = 1 / 2 (one key per thread): they are the block
-// keys, summed from `partials` (BP scale blocks per 64 columns) at load.
-template <int KPT, int BP>
-__global__ __launch_bounds__(kSelThreads) void select_top_kernel(const uint64_t* __restrict__ keys,
+// BLOCKS: the keys (at most 1024) are the block keys, summed here from `partials` and left in `keys`.
+template <bool BLOCKS>
+__global__ __launch_bounds__(kSelThreads) void select_top_kernel(uint64_t* __restrict__ keys,
                                                                  const double* __restrict__ partials,
-                                                                 int64_t m, int64_t d, int64_t n, int64_t k,
+                                                                 int64_t m, int64_t d, int n, uint32_t k,
                                                                  uint8_t* __restrict__ bits,
                                                                  uint8_t* __restrict__ bits_copy) {
-  static_assert(BP == 0 || KPT == 1, "block keys are summed at load one per thread");
-  constexpr int kKeysPerThread = KPT;
   constexpr int NW = kSelThreads / 64;
-  constexpr int HW = kLdsCopies * 257;  // one pass's histogram: hist.h copies of 256 bins
-  __shared__ uint32_t hists[2][HW];  // pass p counts into hists[p & 1] while the other is cleared
-  __shared__ uint32_t ch[3];
-  __shared__ uint32_t tcnt[kKeysPerThread][NW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint64_t kr[kKeysPerThread];
-#pragma unroll
-  for (int q = 0; q < kKeysPerThread; ++q) {
-    const int64_t i = (int64_t)q * kSelThreads + tid;
-    if constexpr (BP == 0) kr[q] = i < n ? keys[i] : 0;
-    else kr[q] = i < n ? (uint64_t)__double_as_longlong(block_key<BP>(partials, m, d, i)) : 0;
-  }
+  constexpr int BITS = 10, NB = 1 << BITS;   // one bin per thread
+  constexpr int HW = kLdsCopies * (NB + 1);  // hist.h copies
+  constexpr int LOW = 31;                    // key bits below t
+  static_assert(NW == 16, "one row of lanes holds the waves' values");
+  static_assert(NB == kSelThreads, "thread t chooses among the digits at bin NB - 1 - t");
+  __shared__ uint32_t tk[kMaxTopKeys];
+  __shared__ uint32_t hist[HW];
+  __shared__ uint32_t wsum[NW], red_min[NW], red_max[NW], red_low[NW];
+  __shared__ uint32_t list[kSelThreads];
+  __shared__ uint64_t few[64];
   __shared__ uint64_t found;
-  // Candidates: once the keys that share the threshold's digits so far fit one per thread,
-  // they are gathered into LDS (in any order: the passes only count them) and the remaining
-  // passes read one slot instead of KPT.
-  __shared__ uint64_t cand[kSelThreads];
-  __shared__ uint32_t ncand;
+  __shared__ uint32_t ch[3], fch[2], nlist, nfew;
+  __shared__ uint32_t tcnt[kMaxTopKeys / 64];  // [slot][wave]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = (1ull << lane) - 1ull;  // lanes before this one
-  bool compact = false;
-  uint32_t nc = 0;
-  // Bits on which all keys agree decide nothing: the OR and AND of the keys bound the digit
-  // passes to the byte-aligned span [s_bot, s_top + 8) holding every differing bit (the first
-  // pass then splits the keys instead of finding them all in one bin); above it lies the
-  // prefix of every key, below it the tail of every key.
-  __shared__ uint64_t red_or[NW], red_and[NW];
-  uint64_t kor = 0, kand = ~0ull;
-#pragma unroll
-  for (int q = 0; q < kKeysPerThread; ++q) {
-    const int64_t i = (int64_t)q * kSelThreads + tid;
-    if (i < n) { kor |= kr[q]; kand &= kr[q]; }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    kor |= __shfl_xor(kor, off, 64);
-    kand &= __shfl_xor(kand, off, 64);
-  }
-  if (lane == 0) { red_or[wave] = kor; red_and[wave] = kand; }
-  __syncthreads();
-  kor = 0; kand = ~0ull;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) { kor |= red_or[w]; kand &= red_and[w]; }
-  const uint64_t diff = kor ^ kand;  // bits that differ between some two keys
-  const int s_top = diff ? (63 - __builtin_clzll(diff)) / 8 * 8 : 0;
-  const int s_bot = diff ? __builtin_ctzll(diff) / 8 * 8 : 8;  // no pass when all keys are equal
-  const uint64_t above = s_top + 8 < 64 ? ~((1ull << (s_top + 8)) - 1ull) : 0ull;
-  uint64_t prefix = kand & above, mask = above;
-  uint32_t krem = (uint32_t)k;
-  bool single = false;
-  for (int i = tid; i < 2 * HW; i += kSelThreads) hists[i / HW][i % HW] = 0;
-  __syncthreads();
-  // Two barriers per pass: after the counts, and after the digit choice (which one wave makes
-  // with a wave scan, while other threads clear the next pass's histogram).
-  int pass = 0;
-  for (int shift = s_top; shift >= s_bot; shift -= 8, ++pass) {
-    uint32_t* hist = hists[pass & 1];
-    if (compact) {
-      const uint64_t c = tid < (int)nc ? cand[tid] : 0;
-      hist_add_copies(hist, 256, (uint32_t)((c >> shift) & 255u), tid < (int)nc && (c & mask) == prefix);
+  constexpr uint64_t kLowMask = (1ull << LOW) - 1ull;
+
+  for (int i = tid; i < HW; i += kSelThreads) hist[i] = 0;
+  if (tid == 0) { nlist = 0; nfew = 0; }
+  // tbase: one less than the smallest nonzero t; low: the OR of the bits below t
+  uint32_t tbase = ~0u, tmax = 0, low = 0;
+  if constexpr (BLOCKS) {
+    if (tid < n) {
+      const uint64_t key = (uint64_t)__double_as_longlong(block_key<1>(partials, m, d, tid));
+      keys[tid] = key;
+      tk[tid] = tmax = (uint32_t)(key >> LOW);
+      tbase = tmax - 1u;  // 0 wraps to the top
+      low = (uint32_t)(key & kLowMask);
     } else {
+      tk[tid] = 0;
+    }
+  } else {
+    constexpr int U = 10;  // loads in flight per thread
+    for (int i0 = tid; i0 - tid < n; i0 += U * kSelThreads) {
+      uint64_t v[U];
 #pragma unroll
-      for (int q = 0; q < kKeysPerThread; ++q) {
-        const int64_t i = (int64_t)q * kSelThreads + tid;
-        hist_add_copies(hist, 256, (uint32_t)((kr[q] >> shift) & 255u), i < n && (kr[q] & mask) == prefix);
+      for (int u = 0; u < U; ++u) v[u] = i0 + u * kSelThreads < n ? keys[i0 + u * kSelThreads] : 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t t = (uint32_t)(v[u] >> LOW);
+        if (u * kSelThreads + i0 - tid < n) tk[i0 + u * kSelThreads] = t;  // past n: 0
+        tbase = min(tbase, t - 1u);
+        tmax = max(tmax, t);
+        low |= (uint32_t)(v[u] & kLowMask);
+      }
+    }
+  }
+  const auto umin = [](uint32_t x, uint32_t y) { return min(x, y); };
+  const auto umax = [](uint32_t x, uint32_t y) { return max(x, y); };
+  const auto uor = [](uint32_t x, uint32_t y) { return x | y; };
+  const auto uadd = [](uint32_t x, uint32_t y) { return x + y; };
+  tbase = wave_scan(tbase, ~0u, umin);
+  tmax = wave_scan(tmax, 0u, umax);
+  low = wave_scan(low, 0u, uor);
+  if (lane == 63) { red_min[wave] = tbase; red_max[wave] = tmax; red_low[wave] = low; }
+  __syncthreads();  // also ends the clearing
+  tbase = lane_value(row_scan(red_min[lane % NW], ~0u, umin), NW - 1);
+  tmax = lane_value(row_scan(red_max[lane % NW], 0u, umax), NW - 1);
+  low = lane_value(row_scan(red_low[lane % NW], 0u, uor), NW - 1);
+  // no key has a bit below t (sums of few-bit squares often have none): the passes end there
+  const int end = low ? 0 : LOW;
+  const uint32_t top = tmax ? tmax - tbase : 0u;
+  // f(slot, item, t) for the slots in batches of B, whose LDS reads are issued together.  The items
+  // past n in the last slot count as further zero keys: they rank after every real one.
+  constexpr int B = 5;
+  auto each = [&](auto f) {
+#pragma unroll 1
+    for (int q0 = 0; q0 * kSelThreads < n; q0 += B) {
+      uint32_t t[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) t[u] = (q0 + u) * kSelThreads < n ? tk[(q0 + u) * kSelThreads + tid] : 0u;
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if ((q0 + u) * kSelThreads < n) f(q0 + u, (q0 + u) * kSelThreads + tid, t[u]);
+    }
+  };
+
+  // threshold T (in the terms (t' << LOW) + low bits): the keys above it are kept, and krem of the
+  // `ties` equal to it, in index order
+  uint64_t T = 0;
+  const int slots = (n + kSelThreads - 1) / kSelThreads;
+  uint32_t krem = k, ties = (uint32_t)(slots * kSelThreads);
+  int shift = LOW + (top ? 32 - __builtin_clz(top) : 0);  // bits not yet fixed
+  uint64_t prefix = 0;                                     // T's fixed bits, shifted down by `shift`
+  uint64_t mine = 0;                                       // this thread's gathered key
+  bool first = true, gathered = false, have = false;
+  if (k == 0) shift = end;
+#pragma unroll 1
+  while (shift > end) {
+    const int s2 = max(shift - BITS, shift > LOW ? LOW : 0);
+    const uint32_t dm = (1u << (shift - s2)) - 1u;
+    if (first && shift > LOW) {  // every key counts; t becomes t'
+      each([&](int, int i, uint32_t t) {
+        t = max(t, tbase) - tbase;
+        tk[i] = t;
+        hist_add_copies(hist, NB, t >> (s2 - LOW), true);
+      });
+      first = false;
+    } else if (gathered) {
+      hist_add_copies(hist, NB, (uint32_t)(mine >> s2) & dm, have);
+    } else if (shift > LOW) {
+      each([&](int, int, uint32_t t) {
+        hist_add_copies(hist, NB, (t >> (s2 - LOW)) & dm, t >> (shift - LOW) == (uint32_t)prefix);
+      });
+    } else {  // more than 1024 keys agree in t'
+      const uint32_t tt = (uint32_t)(prefix >> (LOW - shift));
+#pragma unroll 1
+      for (int i = tid; i < n; i += kSelThreads) {
+        if (tk[i] != tt) continue;
+        const uint64_t v = ((uint64_t)tt << LOW) | (keys[i] & kLowMask);
+        hist_add_copies(hist, NB, (uint32_t)(v >> s2) & dm, v >> shift == prefix);
       }
     }
     __syncthreads();
-    if (wave == 0) {
-      choose_digit_wave(hist, krem, ch);
-    } else {
-      for (int i = tid - 64; i < HW; i += kSelThreads - 64)
-        hists[(pass + 1) & 1][i] = 0;  // read by no one since the previous pass's choice
+    // digit choice: thread t holds bin NB - 1 - t, and clears it for the next pass
+    const uint32_t sum = hist_sum_copies(hist, NB, NB - 1 - tid);
+#pragma unroll
+    for (int c = 0; c < kLdsCopies; ++c) hist[c * (NB + 1) + NB - 1 - tid] = 0;
+    const uint32_t incl = wave_scan(sum, 0u, uadd);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    const uint32_t before = row_scan(lane < wave ? wsum[lane % NW] : 0u, 0u, uadd);  // lower waves' sums
+    const uint32_t over = lane_value(before, NW - 1) + incl - sum;  // keys in higher bins
+    if (over < krem && krem <= over + sum) {
+      ch[0] = (uint32_t)(NB - 1 - tid);
+      ch[1] = krem - over;
+      ch[2] = sum;
     }
     __syncthreads();
-    prefix |= (uint64_t)ch[0] << shift;
+    prefix = (prefix << (shift - s2)) | ch[0];
     krem = ch[1];
-    mask |= (uint64_t)255 << shift;
-    const uint32_t in_bin = ch[2];  // keys sharing the threshold's digits so far
-    if (in_bin == 1 && shift > s_bot) {
-      // a single key has this prefix: it is the threshold (krem = 1), no further digit needed
-      if (compact) {
-        if (tid < (int)nc && (cand[tid] & mask) == prefix) found = cand[tid];
-      } else {
-#pragma unroll
-        for (int q = 0; q < kKeysPerThread; ++q) {
-          const int64_t i = (int64_t)q * kSelThreads + tid;
-          if (i < n && (kr[q] & mask) == prefix) found = kr[q];
+    ties = ch[2];
+    shift = s2;
+    have = have && mine >> shift == prefix;
+    if (shift == end) break;
+    if (!gathered && shift >= LOW && ties <= (uint32_t)kSelThreads) {
+      // the candidates' indices, in any order (what follows only counts them), then their keys
+      const int ts = shift - LOW;
+      const uint32_t p = (uint32_t)prefix;
+      uint32_t cnt = 0;
+      each([&](int, int, uint32_t t) { cnt += t >> ts == p; });
+      const uint32_t upto = wave_scan(cnt, 0u, uadd);
+      uint32_t base = 0;
+      if (lane == 63 && upto) base = atomicAdd(&nlist, upto);
+      base = lane_value(base, 63) + upto - cnt;
+      each([&](int, int i, uint32_t t) {
+        if (t >> ts == p) list[base++] = (uint32_t)i;
+      });
+      __syncthreads();
+      have = tid < (int)ties;
+      if (have) {
+        const uint32_t i = list[tid];
+        mine = ((uint64_t)tk[i] << LOW) | ((int)i < n ? keys[i] & kLowMask : 0);
+      }
+      gathered = true;
+    }
+    if (gathered && ties <= 64u) {
+      if (have) few[atomicAdd(&nfew, 1u)] = mine;
+      __syncthreads();
+      if (wave == 0) {
+        const bool in = lane < (int)ties;
+        const uint64_t x = in ? few[lane] : 0;
+        uint32_t more = 0, same = 0;
+#pragma unroll 8
+        for (uint32_t i = 0; i < ties; ++i) {
+          const uint64_t o = few[i];
+          more += o > x;
+          same += o == x;
+        }
+        if (in && more < krem && krem <= more + same) {  // equal keys write equal values
+          found = x;
+          fch[0] = krem - more;
+          fch[1] = same;
         }
       }
       __syncthreads();
-      prefix = found;
-      single = true;
-      break;
+      prefix = found >> end;
+      krem = fch[0];
+      ties = fch[1];
+      shift = end;
     }
-    if (KPT > 1 && !compact && in_bin <= (uint32_t)kSelThreads && shift > s_bot) {
-      if (tid == 0) ncand = 0;
+  }
+  T = prefix << end;
+  const uint32_t Tt = (uint32_t)(T >> LOW);
+  const bool rank_ties = krem != 0 && krem != ties;  // else all or none of them are kept
+  // Where bits below t' count, the keys with T's t' get their order against T into t: one up, one
+  // down or as it is.  (No key but 0 is below 2^-1000 and t = ~0 would be a NaN of all ones: neither
+  // step wraps.)
+  if (end == 0 && k != 0) {
+    auto settle = [&](int i, uint64_t v) { tk[i] += v > T ? 1u : v < T ? ~0u : 0u; };
+    if (gathered) {
       __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kKeysPerThread; ++q) {
-        const int64_t i = (int64_t)q * kSelThreads + tid;
-        const bool c = i < n && (kr[q] & mask) == prefix;
-        const uint64_t b = __ballot(c);
-        uint32_t base = 0;
-        if (lane == 0 && b) base = atomicAdd(&ncand, (uint32_t)__popcll(b));
-        base = __shfl(base, 0, 64);
-        if (c) cand[base + (uint32_t)__popcll(b & below)] = kr[q];
+      if (tid < (int)nlist && (uint32_t)(mine >> LOW) == Tt) settle((int)list[tid], mine);
+    } else {
+#pragma unroll 1
+      for (int i = tid; i < n; i += kSelThreads)
+        if (tk[i] == Tt) settle(i, ((uint64_t)Tt << LOW) | (keys[i] & kLowMask));
+    }
+    __syncthreads();
+  }
+  if (rank_ties) {
+    uint32_t c = 0;  // lane q: slot q's ties in this wave
+    each([&](int q, int, uint32_t t) {
+      const uint32_t b = (uint32_t)__popcll(__ballot(t == Tt));
+      c = lane == q ? b : c;
+    });
+    if (lane < slots) tcnt[lane * NW + wave] = c;
+    __syncthreads();
+    // exclusive prefix of the tie counts in index order (slot-major, then wave), by wave 0
+    if (wave == 0) {
+      uint32_t run = 0;
+#pragma unroll 1
+      for (int e0 = 0; e0 < slots * NW; e0 += 64) {
+        const uint32_t v = e0 + lane < slots * NW ? tcnt[e0 + lane] : 0u;
+        const uint32_t incl = wave_scan(v, 0u, uadd);
+        if (e0 + lane < slots * NW) tcnt[e0 + lane] = run + incl - v;
+        run += lane_value(incl, 63);
       }
-      __syncthreads();
-      nc = ncand;
-      compact = true;
     }
+    __syncthreads();
   }
-  // threshold key (the common tail completes it); krem of its ties are kept, in index order
-  const uint64_t T = single ? prefix : (prefix | (kand & ((1ull << s_bot) - 1ull)));
-  uint64_t tb[kKeysPerThread];  // tie ballots per slot
-#pragma unroll
-  for (int q = 0; q < kKeysPerThread; ++q) {
-    const int64_t i = (int64_t)q * kSelThreads + tid;
-    tb[q] = __ballot(i < n && kr[q] == T);
-    if (lane == 0) tcnt[q][wave] = (uint32_t)__popcll(tb[q]);
-  }
-  __syncthreads();
-  // exclusive prefix of the tie counts in index order (slot-major, then wave), by wave 0
-  constexpr int NTC = kKeysPerThread * NW, PL = (NTC + 63) / 64;
-  if (wave == 0) {
-    uint32_t* flat = &tcnt[0][0];
-    uint32_t v[PL], sum = 0;
-#pragma unroll
-    for (int e = 0; e < PL; ++e) {
-      v[e] = lane * PL + e < NTC ? flat[lane * PL + e] : 0u;
-      sum += v[e];
-    }
-    uint32_t incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += y;
-    }
-    uint32_t run = incl - sum;
-#pragma unroll
-    for (int e = 0; e < PL; ++e) {
-      if (lane * PL + e < NTC) flat[lane * PL + e] = run;
-      run += v[e];
-    }
-  }
-  __syncthreads();
-  // keep bits: a wave's 64 keys are 8 whole bytes; wave-uniform stores of 8 bytes where the
-  // keys and the pointer allow it, else one byte per 8 lanes
-  const bool wide = ((uintptr_t)bits % 8 == 0) && (bits_copy == nullptr || (uintptr_t)bits_copy % 8 == 0);
-#pragma unroll
-  for (int q = 0; q < kKeysPerThread; ++q) {
-    const int64_t i0 = (int64_t)q * kSelThreads + wave * 64, i = i0 + lane;
-    if (i0 >= n) continue;  // wave-uniform
-    const bool in = i < n, tie = ((tb[q] >> lane) & 1ull) != 0;
-    const uint32_t rank = tie ? tcnt[q][wave] + (uint32_t)__popcll(tb[q] & below) : 0u;
-    const bool keep = in && (kr[q] > T || (tie && rank < krem));
-    const uint64_t bal = __ballot(keep);
+  // keep bits: lane q takes slot q's 8 bytes of this wave's keys
+  const uint64_t ties_kept = krem != 0 && !rank_ties ? ~0ull : 0ull;
+  const uint32_t r0 = rank_ties && lane < slots ? tcnt[lane * NW + wave] : 0u;
+  uint64_t mask = 0;
+  each([&](int q, int, uint32_t t) {
+    const uint64_t eq = __ballot(t == Tt);
+    uint64_t bal = __ballot(t > Tt) | (eq & ties_kept);
+    if (rank_ties && eq != 0)
+      bal |= __ballot(t == Tt && lane_value(r0, q) + (uint32_t)__popcll(eq & below) < krem);
+    mask = lane == q ? bal : mask;
+  });
+  if (k == 0) mask = 0;
+  const int i0 = lane * kSelThreads + wave * 64;
+  if (lane < slots && i0 < n) {
+    const bool wide = ((uintptr_t)bits % 8 == 0) && (bits_copy == nullptr || (uintptr_t)bits_copy % 8 == 0);
     if (wide && i0 + 64 <= n) {
-      if (lane == 0) {
-        *reinterpret_cast<uint64_t*>(bits + (i0 >> 3)) = bal;
-        if (bits_copy) *reinterpret_cast<uint64_t*>(bits_copy + (i0 >> 3)) = bal;
+      *reinterpret_cast<uint64_t*>(bits + (i0 >> 3)) = mask;
+      if (bits_copy) *reinterpret_cast<uint64_t*>(bits_copy + (i0 >> 3)) = mask;
+    } else {
+      for (int e = 0; e < 64 && i0 + e < n; e += 8) {
+        bits[(i0 + e) >> 3] = (uint8_t)(mask >> e);
+        if (bits_copy) bits_copy[(i0 + e) >> 3] = (uint8_t)(mask >> e);
       }
-    } else if ((lane & 7) == 0 && in) {
-      const uint8_t byte = (uint8_t)(bal >> lane);
-      bits[i >> 3] = byte;
-      if (bits_copy) bits_copy[i >> 3] = byte;
     }
   }
 }
 
 // ---------------------------------------------------------------------------------------
-// The same top-k for more keys than the registers hold (n > kKeysPerThread * kSelThreads):
+// The same top-k for more keys than select_top_kernel's LDS holds (n > kMaxTopKeys):
 // each radix pass streams the keys from global memory (they stay in L2), and the threshold's
 // ties are ranked in index order chunk by chunk (1024 consecutive keys per chunk, one per
 // thread, a workgroup scan per chunk).  One workgroup, so no cross-workgroup protocol.
@@ -502,17 +651,13 @@ __global__ __launch_bounds__(kSelThreads) void select_top_stream_kernel(const ui
   }
 }
 
-void launch_top(const double* keys, int64_t n, int64_t k, uint8_t* bits, uint8_t* bits_copy, hipStream_t s) {
-  const uint64_t* kk = (const uint64_t*)keys;
-#define RESQ_TOP(KPT)                                                                                \
-  if (n <= (int64_t)(KPT) * kSelThreads) {                                                          \
-    hipLaunchKernelGGL((select_top_kernel<KPT, 0>), dim3(1), dim3(kSelThreads), 0, s, kk, (const double*)nullptr, \
-                       (int64_t)0, (int64_t)0, n, k, bits, bits_copy);                                \
-    return;                                                                                          \
-  }
-  RESQ_TOP(1) RESQ_TOP(2) RESQ_TOP(4) RESQ_TOP(8) RESQ_TOP(16) RESQ_TOP(kKeysPerThread)
-#undef RESQ_TOP
-  hipLaunchKernelGGL(select_top_stream_kernel, dim3(1), dim3(kSelThreads), 0, s, kk, n, k, bits, bits_copy);
+void launch_top(double* keys, int64_t n, int64_t k, uint8_t* bits, uint8_t* bits_copy, hipStream_t s) {
+  uint64_t* kk = (uint64_t*)keys;
+  if (n <= kMaxTopKeys)
+    hipLaunchKernelGGL((select_top_kernel<false>), dim3(1), dim3(kSelThreads), 0, s, kk, (const double*)nullptr,
+                       (int64_t)0, (int64_t)0, (int)n, (uint32_t)k, bits, bits_copy);
+  else
+    hipLaunchKernelGGL(select_top_stream_kernel, dim3(1), dim3(kSelThreads), 0, s, (const uint64_t*)kk, n, k, bits, bits_copy);
 }
 
 // Block keys, then the top-k over them.  HiF4 blocks up to one per thread: the top-k sums the
@@ -523,8 +668,8 @@ void launch_block_top(int fmt, const double* partials, int64_t m, int64_t d, int
                       uint8_t* bits_copy, hipStream_t s) {
   const int64_t nb = ((m + 31) / 32) * (d / 64);
   if (fmt == 1 && nb <= kSelThreads) {
-    hipLaunchKernelGGL((select_top_kernel<1, 1>), dim3(1), dim3(kSelThreads), 0, s, (const uint64_t*)nullptr,
-                       partials, m, d, nb, keep, ws.group_bits, bits_copy);
+    hipLaunchKernelGGL((select_top_kernel<true>), dim3(1), dim3(kSelThreads), 0, s, (uint64_t*)ws.keys, partials,
+                       m, d, (int)nb, (uint32_t)keep, ws.group_bits, bits_copy);
     return;
   }
   const dim3 g((unsigned)((nb + kThreads - 1) / kThreads));
@@ -612,41 +757,16 @@ __device__ __forceinline__ ThreadWords thread_words(const uint8_t* codes, const 
   return t;
 }
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
-// HiF4 keys of word Q of a thread's four (its elements 8Q .. 8Q + 7, one level-2 group and two
-// level-3 groups): value k (4 + m) 2^(e - 35 - b).  The eight magnitudes k spread to the bytes
-// of two dwords, one 16-bit-lane multiply by 4 + m forms four products k (4 + m) <= 49 at once
-// (no carry crosses a byte), each byte converts to float32 exactly, and ldexp applies the
-// group's 2^(e - 35 - b) (exact: the smallest nonzero value, 4 * 2^-37, is normal).  f2 holds
-// 4 + m in both 16-bit lanes, e35 = e - 35; l2 and l3 are the thread's level-2 and level-3
-// shift bits, from its first group on.
-template <int Q>
-__device__ __forceinline__ void hif4_word_keys(uint32_t cw, uint32_t f2, int e35, uint32_t l2, uint32_t l3,
-                                               uint32_t key[8]) {
-  const uint32_t ta = __builtin_amdgcn_perm(cw, cw, 0x0C010C00u), tb = __builtin_amdgcn_perm(cw, cw, 0x0C030C02u);
-  const uint32_t ka = (ta | (ta << 4)) & 0x07070707u, kb = (tb | (tb << 4)) & 0x07070707u;
-  const uint32_t pa = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, ka) * __builtin_bit_cast(u16x2, f2));
-  const uint32_t pb = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, kb) * __builtin_bit_cast(u16x2, f2));
-  const int b2 = (int)((l2 >> Q) & 1u);
-  const int ea = e35 - b2 - (int)((l3 >> (2 * Q)) & 1u), eb = e35 - b2 - (int)((l3 >> (2 * Q + 1)) & 1u);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    key[i] = __float_as_uint(ldexpf((float)((pa >> (8 * i)) & 0xFFu), ea));
-    key[4 + i] = __float_as_uint(ldexpf((float)((pb >> (8 * i)) & 0xFFu), eb));
-  }
-}
-
 template <int FMT>
 __device__ __forceinline__ void thread_keys(const ThreadWords& t, uint32_t key[32]) {
   if constexpr (FMT == 1) {
     const uint32_t f2 = (4u + (t.sc & 3u)) * 0x00010001u;
     const int e35 = (int)((t.sc >> 2) & 63u) - 35;
     const uint32_t l2 = t.sc >> (8 + t.jpos / 8), l3 = t.sc >> (16 + t.jpos / 4);
-    hif4_word_keys<0>(t.cw.x, f2, e35, l2, l3, key);
-    hif4_word_keys<1>(t.cw.y, f2, e35, l2, l3, key + 8);
-    hif4_word_keys<2>(t.cw.z, f2, e35, l2, l3, key + 16);
-    hif4_word_keys<3>(t.cw.w, f2, e35, l2, l3, key + 24);
+    hif4_word_keys(t.cw.x, f2, e35, l2, l3, 0, key);
+    hif4_word_keys(t.cw.y, f2, e35, l2, l3, 1, key + 8);
+    hif4_word_keys(t.cw.z, f2, e35, l2, l3, 2, key + 16);
+    hif4_word_keys(t.cw.w, f2, e35, l2, l3, 3, key + 24);
   } else {
     mx_word_keys(t.cw.x, t.sc, key);
     mx_word_keys(t.cw.y, t.sc, key + 8);
