@@ -176,6 +176,14 @@ __device__ __forceinline__ void finish_tile(const GemmParams& p, v16f (&acc)[TM]
   float* slot = reinterpret_cast<float*>(smem) + (size_t)wt * (KG > 1 ? TM * TN * 16 * 64 : 8 * RW);
   const int half = lane >> 5, l32 = lane & 31;
   const int64_t col0 = ((int64_t)N0 + wn * TN) * 32;
+  // read once: past each memory clobber below the parameters, and what is computed from them, would
+  // be formed again
+  const int64_t M = p.M, N = p.N, ldy = p.ldy;
+  const int out_bf16 = p.out_bf16;
+  void* const Y = p.Y;
+  bool wide[TN];  // a lane's columns of store s: one 16-byte store
+#pragma unroll
+  for (int s = 0; s < TN; ++s) wide[s] = p.vec_y && col0 + (4 * lane + 256 * s) % RW + 3 < N;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -191,13 +199,13 @@ __device__ __forceinline__ void finish_tile(const GemmParams& p, v16f (&acc)[TM]
         const int f = 4 * lane + 256 * s;  // flat float index in the 8 x RW block
         const v4f v = *reinterpret_cast<const v4f*>(slot + f);
         const int64_t row = row0 + f / RW, col = col0 + f % RW;
-        if (row < p.M) {
-          if (p.vec_y && col + 3 < p.N) {
-            store_y4(p.Y, row * p.ldy + col, v, p.out_bf16);
+        if (row < M) {
+          if (wide[s]) {
+            store_y4(Y, row * ldy + col, v, out_bf16);
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (col + e < p.N) store_y(p.Y, row * p.ldy + col + e, v[e], p.out_bf16);
+              if (col + e < N) store_y(Y, row * ldy + col + e, v[e], out_bf16);
           }
         }
       }
