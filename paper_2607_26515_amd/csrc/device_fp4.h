@@ -150,8 +150,11 @@ __device__ __forceinline__ float hif4_half_fit(float step) { return 3.5f * step;
 // rounds the quotient correctly; and since the grid's midpoints (2j+1)/2 have few bits and
 // float32 values around a midpoint times the step are at least half a place apart in the quotient
 // ((4+m) < 8), a quotient equals a midpoint exactly when x does, so rounding it again to
-// an integer is the rounding of x / step itself.  Checked against the comparison with every
-// midpoint for all finite float32 x, every m and b (host emulation).
+// an integer is the rounding of x / step itself.  Checked in a host emulation against the comparison
+// with every midpoint, every m and b: all float32 x from 2^-4 to 2^5 steps at eight exponents of the
+// scale, strided x elsewhere; and on the GPU over every bf16 x.  The quotient replaced the
+// midpoint searches: HiF4 activation pass of the 7B prefill (m = 8192) 345 -> 259 us, the 3B
+// backward's quantization 350 -> 293 us.
 __device__ __forceinline__ float hif4_round(float x, const Hif4Grid& g) {
   const float lim = 7.f * g.step;
   const float xc = __builtin_amdgcn_fmed3f(x, -lim, lim);

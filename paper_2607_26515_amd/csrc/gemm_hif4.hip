@@ -15,6 +15,12 @@
 // the finished tiles' folds are issued between the MFMAs.  The barrier that publishes the
 // next stage stands before the last row tile's MFMAs, whose operands are in registers, so no
 // wave waits for LDS with an empty matrix pipe.
+//
+// Bound by MFMA issue together with the fold's VALU work (16 FMAs per tile and step) and, at
+// two workgroups per CU, by the stages' copies from L2.  Two E2M3 terms of 48 bytes per lane with
+// E3M2 weights, a step's reads ahead of its MFMAs: 7B prefill GEMMs (m = 8192) 3.69 ms, 3B backward
+// GEMMs (m = 8192) 1.13 ms; as above 3.12 and 0.99 ms.  Without the fold (wrong results) the
+// prefill loop takes 2.84 ms, without copies 2.50 ms.
 #include "gemm_core.h"
 #include "gemm_hif4.h"
 #include "gemm_hif4_geo.h"
