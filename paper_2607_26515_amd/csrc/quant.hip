@@ -348,11 +348,15 @@ __device__ __forceinline__ void store_kmajor8(uint8_t* __restrict__ codes, uint8
 
 // ---------------------------------------------------------------------------------------
 // Q along rows, K-major output: 8 consecutive elements per lane (an MXFP4 block is 4 lanes, a HiF4
-// block 8), 2^lx lanes along a row and 256 >> lx rows at a time, kRowsAhead such steps loaded
-// before the first is quantized.  Bound by HBM for MXFP4 and by VALU issue for HiF4: the four weights
-// of the 3B layer in HiF4 took 95 us with four elements per lane and the midpoint searches, now 79 us.
+// block 8), 2^lx lanes along a row and 256 >> lx rows at a time (lx: launch_quant_rows).  Bound by
+// launch and first-load latency up to about 2^20 elements, above by HBM for MXFP4 and by VALU issue
+// for HiF4.  One row per lane: with four rows loaded and quantized per lane a small matrix filled
+// few workgroups, each of which ran four quantizations in turn.  Kernel times in us, four elements per
+// lane (and searches for the HiF4 codes) -> four rows of eight -> one row of eight: HiF4 256 x 1024
+// 3.0 -> 5.0 -> 3.1, 1024 x 64 (then at least 64 lanes per row) 3.3 -> 8.1 -> 3.1, 16384 x 2048
+// 32.2 -> 24.4 -> 21.6; MXFP4 256 x 1024 3.1 -> 3.9 -> 3.1, 4096 x 11008 25.2 -> 22.4 -> 19.5, the
+// same from float32 31.1 -> 33.4 -> 31.3.
 // ---------------------------------------------------------------------------------------
-constexpr int kRowsAhead = 4;
 
 // 8 consecutive elements; VEC: 0 single loads, 1 pieces of four elements, 2 (bf16) 16 bytes.
 template <bool F32, int VEC>
@@ -380,39 +384,23 @@ __global__ __launch_bounds__(kThreads) void quant_rows_kernel(const void* __rest
   const int64_t j8 = ((int64_t)blockIdx.x << lx) + tx;
   if (8 * j8 >= cols) return;  // whole blocks drop out together (cols % block == 0)
   constexpr int G = FMT == kMX ? 4 : 8;  // lanes per block
-  // this lane's offsets within a step's rows; the step's first row is uniform
-  const int64_t xoff = ty * ld + 8 * j8, coff = ty * (cols / 2) + 4 * j8, soff = ty * (cols / (8 * G)) + j8 / G;
-  for (int64_t r0 = (int64_t)blockIdx.y * rstep * kRowsAhead; r0 < rows; r0 += (int64_t)gridDim.y * rstep * kRowsAhead) {
-    float v[kRowsAhead][8];
-#pragma unroll
-    for (int u = 0; u < kRowsAhead; ++u) {
-      const int64_t row = r0 + u * rstep;
-      if (row + ty < rows) {
-        load8<F32, VEC>(x, row * ld + xoff, v[u]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[u][i] = 0.f;
-      }
+  for (int64_t row = (int64_t)blockIdx.y * rstep + ty; row < rows; row += (int64_t)gridDim.y * rstep) {
+    float v[8];
+    load8<F32, VEC>(x, row * ld + 8 * j8, v);
+    const Q8<FMT> q = quantize8<FMT>(v);
+    const uint32_t meta = FMT == kMX ? q.scale : hif4_meta8(q.scale, q.b, q.b2);
+    uint8_t* at = codes + row * (cols / 2) + 4 * j8;
+    const uint32_t w = q.nibbles();
+    if (codes4) {  // codes is 4-byte aligned (uniform)
+      *reinterpret_cast<uint32_t*>(at) = w;
+    } else {
+      reinterpret_cast<uint16_t*>(at)[0] = (uint16_t)w;
+      reinterpret_cast<uint16_t*>(at)[1] = (uint16_t)(w >> 16);
     }
-#pragma unroll
-    for (int u = 0; u < kRowsAhead; ++u) {
-      const int64_t row = r0 + u * rstep;
-      const Q8<FMT> q = quantize8<FMT>(v[u]);
-      const uint32_t meta = FMT == kMX ? q.scale : hif4_meta8(q.scale, q.b, q.b2);
-      if (row + ty >= rows) continue;
-      uint8_t* at = codes + row * (cols / 2) + coff;
-      const uint32_t w = q.nibbles();
-      if (codes4) {  // codes is 4-byte aligned (uniform)
-        *reinterpret_cast<uint32_t*>(at) = w;
-      } else {
-        reinterpret_cast<uint16_t*>(at)[0] = (uint16_t)w;
-        reinterpret_cast<uint16_t*>(at)[1] = (uint16_t)(w >> 16);
-      }
-      if ((tx & (G - 1)) == 0) {
-        const int64_t si = row * (cols / (8 * G)) + soff;
-        if constexpr (FMT == kMX) reinterpret_cast<uint8_t*>(scales)[si] = (uint8_t)meta;
-        else reinterpret_cast<uint32_t*>(scales)[si] = meta;
-      }
+    if ((tx & (G - 1)) == 0) {
+      const int64_t si = row * (cols / (8 * G)) + j8 / G;
+      if constexpr (FMT == kMX) reinterpret_cast<uint8_t*>(scales)[si] = (uint8_t)meta;
+      else reinterpret_cast<uint32_t*>(scales)[si] = meta;
     }
   }
 }
@@ -940,10 +928,11 @@ inline unsigned grid_rows(int64_t rows) { return (unsigned)(rows < 65535 ? rows 
 void launch_quant_rows(int fmt, const void* x, bool in_f32, int64_t rows, int64_t cols,
                        int64_t ld, uint8_t* codes, void* scales, hipStream_t s) {
   if (rows == 0 || cols == 0) return;
-  // lanes along a row: enough for the row up to a workgroup, at least a wave's 64
-  int lx = 6;
+  // lanes along a row: the smallest power of two that covers it, from a HiF4 block's 8 (a narrow
+  // row leaves no idle lanes) up to a workgroup
+  int lx = 3;
   while (lx < 8 && (cols / 8) > ((int64_t)1 << lx)) ++lx;
-  const int64_t per = (int64_t)(kThreads >> lx) * kRowsAhead;
+  const int64_t per = kThreads >> lx;
   const dim3 grid((unsigned)((cols / 8 + ((int64_t)1 << lx) - 1) >> lx), grid_rows((rows + per - 1) / per));
   const size_t esz = in_f32 ? 4 : 2;
   const bool vec4 = (uintptr_t)x % (4 * esz) == 0 && ld % 4 == 0, vec8 = (uintptr_t)x % 16 == 0 && ld % 8 == 0;
