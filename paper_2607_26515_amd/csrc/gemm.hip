@@ -214,9 +214,9 @@ void launch_cfg(const GemmParams& p, int n_terms, hipStream_t s) {
 //    byte of B), two workgroups per CU;
 //  - otherwise: 128 x 192 tiles.  HiF4 always takes these: they fit two waves per SIMD (two
 //    workgroups per CU at NS = 2), which hides one workgroup's barriers and epilogue behind
-//    the other's MFMAs; 128 x 256 HiF4 tiles would spill.  When the
-//    HiF4 grid has fewer than two workgroups per CU (M = 256 decode), the tile runs as eight
-//    waves of 32 x 96 instead, so each SIMD still holds two waves.
+//    the other's MFMAs; 128 x 256 HiF4 tiles would spill.  When the HiF4 grid has at most one
+//    workgroup per CU (M = 256 decode), the tile runs as eight waves of 32 x 96 instead, so each
+//    SIMD still holds two waves.
 enum TileCfg { kSmall = 0, kWide = 1, kMid = 2, kMid8 = 3, kNarrow = 4, kStream = 5 };  // kStream + TN - 1
 // output tile rows and columns of the staged configurations
 constexpr int kTileRows[5] = {64, 128, 128, 128, 64}, kTileCols[5] = {64, 256, 192, 192, 128};
@@ -345,8 +345,14 @@ Plan plan(int fmt, int64_t M, int64_t N, int64_t K, bool may_split) {
     pl.tiles = wide ? wgs(4, 8) : wgs(4, 6);
     pl.kg = 1;
     pl.ns = fmt == 0 ? 4 : 2;  // HiF4 fits two workgroups per CU at two stages
-    // HiF4 grids below two workgroups per CU: eight waves per 128 x 192 tile (two per SIMD)
-    if (fmt == 1 && pl.tiles < 2 * kCUs) pl.cfg = kMid8;
+    // HiF4 grids within one workgroup per CU: eight waves per 128 x 192 tile (two per SIMD).
+    // They take 168 registers each (one term; 198 with two), so a CU holds no second workgroup of
+    // them, but two of four waves.  Whole calls in us, eight -> four waves, S_2:4 / no residual: 230
+    // tiles (m = 256, 2048 -> 22016) 35.6 -> 37.9 / 29.5 -> 30.9, 256 tiles (m = 1024, 2048 ->
+    // 6144) 41.1 -> 41.9 / 31.0 -> 31.6; 258 tiles (m = 256, 2048 -> 24700) 58.9 -> 49.5 / 48.0 ->
+    // 37.0, 378 (m = 331, 12288 -> 24150, no residual) 287 -> 187, 508 (m = 512, 3584 -> 24384)
+    // 105.6 -> 97.8 / 81.1 -> 66.4.
+    if (fmt == 1 && pl.tiles <= kCUs) pl.cfg = kMid8;
   }
   return pl;
 }
