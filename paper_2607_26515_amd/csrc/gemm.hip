@@ -272,6 +272,7 @@ Plan plan(int fmt, int64_t M, int64_t N, int64_t K, bool may_split) {
   Plan pl{};
   pl.ksplit = 1;
   pl.kper = nkb;
+  if (M == 0 || N == 0) may_split = false;  // no tiles, whose number divides the CUs below
   if (stream_plan(fmt, M, mt, nt, nkb, may_split, pl)) return pl;
   if (wgs(4, 4) < 240 && may_split && nkb >= 128 && kCUs / wgs(2, 4) >= 2) {
     // small grids with long K (the down projection of a decode batch): 64 x 128 tiles with K

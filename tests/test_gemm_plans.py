@@ -1,9 +1,14 @@
 """The GEMM's plans, as the host-side query reports them (CPU)."""
 import itertools
+import os
+import subprocess
+import sys
 
 import pytest
 
 import paper_2607_26515_amd as P
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.parametrize("m,n", [(257, 25505), (331, 24150), (512, 12800), (896, 10240), (1555, 4640), (1664, 4224),
@@ -24,3 +29,21 @@ def test_hif4_eight_wave_tiles_are_still_used():
         tiles = -(-m // 128) * -(-n // 192)
         if 240 <= -(-m // 128) * -(-n // 128) and tiles <= 256:
             assert P.gemm_plan("hif4", m, n, 2048)["tile"] == "128x192_8w", (m, n)
+
+
+def test_empty_products_have_plans_and_workspaces():
+    """No rows or no columns, over every range of K that the plans tell apart: the queries answer (in
+    a child process, since a division by the number of tiles would end this one)."""
+    code = """
+import paper_2607_26515_amd as P
+for fmt in ("mxfp4", "hif4"):
+    for m, n in ((0, 64), (64, 0), (0, 0), (0, 40000), (8192, 0)):
+        for k in (0, 64, 8192, 32768, 1 << 20):
+            for split in (False, True):
+                assert P.gemm_plan(fmt, m, n, k, split)["ksplit"] == 1
+            for op in range(7):
+                P.resq_workspace_size(op, P.FORMATS[fmt], 2, m, k, n)
+print("done")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "done" in r.stdout, (r.returncode, r.stderr[-500:])
