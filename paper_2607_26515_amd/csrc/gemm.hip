@@ -258,8 +258,16 @@ bool stream_plan(int fmt, int64_t M, int64_t mt, int64_t nt, int64_t nkb, bool m
   pl.kg = waves;
   pl.ns = fmt == 0 ? 2 : 1;
   if (may_split && pl.tiles <= kCUs / 2 && nkb >= 512) {
-    const int64_t ks = std::min(kCUs / pl.tiles, nkb / 128);
-    pl.ksplit = (int)(ks > 8 ? 8 : ks);
+    int64_t ks = std::min({(int64_t)8, kCUs / pl.tiles, nkb / 128});
+    // Within the partial tiles' bytes of the staged plan for this shape (64 x 128 tiles in up to four
+    // splits): a split must not take a call over the caller's or the library's scratch.  HiF4 stays
+    // below it by its smaller activation records.  (m = 128, 131072 -> 256: 90 us staged, 33 in eight
+    // splits, 37 in the four that fit; m = 64, 65536 -> 256 50.5, 21.9, 22.6.)
+    if (fmt == 0) {
+      const int64_t t = ((mt + 1) / 2) * ((nt + 3) / 4), staged = t * std::min((int64_t)4, kCUs / t) * (64 * 128);
+      ks = std::min(ks, staged / (pl.tiles * tn * 1024));
+    }
+    pl.ksplit = (int)ks;
     pl.kper = (nkb + pl.ksplit - 1) / pl.ksplit;
     pl.partial_bytes = (size_t)pl.tiles * pl.ksplit * (tn * 1024) * sizeof(float);
   }

@@ -47,3 +47,33 @@ print("done")
 """
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "done" in r.stdout, (r.returncode, r.stderr[-500:])
+
+
+def _scratch_bound(fmt, m, n, d, terms):
+    """The activation operands (lane records of 16 bytes MXFP4, 48 bytes HiF4, one scale byte each) and
+    the K-split partial tiles of 64 x 128 outputs in up to four splits, 256-byte aligned."""
+    def al(x):
+        return -(-x // 256) * 256
+    lanes = -(-m // 32) * -(-d // 64) * 64
+    tiles = -(-m // 64) * -(-n // 128)
+    return terms * (al(lanes * (16 if fmt == "mxfp4" else 48)) + al(lanes)) + tiles * min(4, 256 // tiles) * 64 * 128 * 4
+
+
+@pytest.mark.parametrize("fmt", ["mxfp4", "hif4"])
+@pytest.mark.parametrize("sp,terms", [("none", 1), ("2:4", 2)])
+def test_streamed_splits_keep_the_scratch_bound(fmt, sp, terms):
+    """A K split of the 32-row tiles takes no more scratch than one of 64 x 128 tiles in four
+    splits: calls at the limit of the library's own scratch stay accepted."""
+    for m, n, d in itertools.product((1, 8, 32, 33, 64, 65, 96, 97, 128, 160, 200, 229, 256), (1, 32, 33, 64, 96, 113, 256, 400, 510),
+                                     (32768, 40960, 65536, 131072)):
+        if P.gemm_plan(fmt, m, n, d)["ksplit"] == 1:
+            continue
+        need = P.resq_workspace_size(P.OP_LINEAR_FWD_PREPARED, P.FORMATS[fmt], P.sparsity_code(sp), m, d, n)
+        assert need <= _scratch_bound(fmt, m, n, d, terms), (m, n, d, need)
+
+
+def test_noalloc_limit_is_not_passed_by_a_split():
+    """Forward calls that fit the library's scratch with the 64 x 128 tiles' partials."""
+    for m, d, n in ((97, 350528, 96), (97, 350528, 128), (98, 348096, 256)):
+        need = P.resq_workspace_size(P.OP_LINEAR_FWD_PREPARED, P.FORMATS["mxfp4"], P.sparsity_code("unstructured50"), m, d, n)
+        assert need <= P.NOALLOC_SCRATCH_BYTES, (m, d, n, need)
