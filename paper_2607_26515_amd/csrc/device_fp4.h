@@ -145,28 +145,26 @@ __device__ __forceinline__ Hif4Grid hif4_grid(int c1, float inv_q, int b) {
 // shift b: 7 (4+m) 2^(e-36-b) = 3.5 step (exact).
 __device__ __forceinline__ float hif4_half_fit(float step) { return 3.5f * step; }
 
-// x on that grid: the signed integer k (-7 .. 7, with x's sign when zero) nearest to x / step,
-// ties to even k, saturating.  inv is the correctly rounded reciprocal, so one residual step
-// rounds the quotient correctly; and since the grid's midpoints (2j+1)/2 have few bits and
-// float32 values around a midpoint times the step are at least half a place apart in the quotient
-// ((4+m) < 8), a quotient equals a midpoint exactly when x does, so rounding it again to
-// an integer is the rounding of x / step itself.  Checked in a host emulation against the comparison
-// with every midpoint, every m and b: all float32 x from 2^-4 to 2^5 steps at eight exponents of the
-// scale, strided x elsewhere; and on the GPU over every bf16 x.  The quotient replaced the
-// midpoint searches: HiF4 activation pass of the 7B prefill (m = 8192) 345 -> 259 us, the 3B
-// backward's quantization 350 -> 293 us.
+// |x| on that grid: the integer k (0 .. 7) nearest to |x| / step, ties to even k, saturating; NaN
+// gives 0 (the median of a NaN and two numbers is the smaller number).  inv is the correctly rounded
+// reciprocal, so one residual step rounds the quotient correctly; and since the grid's midpoints
+// (2j+1)/2 have few bits and float32 values around a midpoint times the step are at least half a
+// place apart in the quotient ((4+m) < 8), a quotient equals a midpoint exactly when |x| does, so
+// rounding it again to an integer is the rounding of |x| / step itself.  tests/hif4_round_check.cpp
+// compares it on the host with every midpoint; the GPU tests run every bf16 x.  The quotient
+// replaced midpoint searches: HiF4 activation pass of the 7B prefill (m = 8192) 345 -> 259 us, the
+// 3B backward's quantization 350 -> 293 us.
 __device__ __forceinline__ float hif4_round(float x, const Hif4Grid& g) {
-  const float lim = 7.f * g.step;
-  const float xc = __builtin_amdgcn_fmed3f(x, -lim, lim);
-  const float y = xc * g.inv;
-  return __builtin_rintf(fmaf(-fmaf(y, g.step, -xc), g.inv, y));  // in this form -0 stays -0
+  const float a = __builtin_amdgcn_fmed3f(fabsf(x), 0.f, 7.f * g.step);
+  const float y = a * g.inv;
+  return __builtin_rintf(fmaf(-fmaf(y, g.step, -a), g.inv, y));
 }
-// The 4-bit codes of four elements, one per byte (high nibbles zero): |k| and the sign of x.
+// The 4-bit codes of four elements, one per byte (high nibbles zero): k and the sign of x.
 __device__ __forceinline__ uint32_t hif4_code_bytes(const float k[4], const float x[4]) {
-  uint32_t n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[0]), 0u, 0u);
-  n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[1]), 1u, n);
-  n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[2]), 2u, n);
-  n = __builtin_amdgcn_cvt_pk_u8_f32(fabsf(k[3]), 3u, n);
+  uint32_t n = __builtin_amdgcn_cvt_pk_u8_f32(k[0], 0u, 0u);
+  n = __builtin_amdgcn_cvt_pk_u8_f32(k[1], 1u, n);
+  n = __builtin_amdgcn_cvt_pk_u8_f32(k[2], 2u, n);
+  n = __builtin_amdgcn_cvt_pk_u8_f32(k[3], 3u, n);
   const uint32_t s = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x0C0C0703u) |
                      __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07030C0Cu);
   return n | ((s >> 4) & 0x08080808u);

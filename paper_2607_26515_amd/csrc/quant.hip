@@ -169,15 +169,16 @@ template <int FMT>
 struct Q8 {
   uint32_t w;      // MXFP4: the codes as nibbles, element 2i in the low nibble of byte i
   uint32_t nb[2];  // HiF4: the codes of elements 4h .. 4h+3 in the low nibbles of nb[h]'s bytes
-  float v[8];      // MXFP4: the values; HiF4: the signed integers k (value k * step)
+  float v[8];      // MXFP4: the values; HiF4: the integers k (magnitude k * step)
   float step[2];   // HiF4: grid step of elements 4h .. 4h+3
   uint32_t scale;  // scale byte: MXFP4 E8M0, HiF4 level-1 code
   int b[2], b2;    // HiF4: level-2 + level-3 shift of elements 4h .. 4h+3, level-2 bit
 
-  __device__ __forceinline__ float value(int i) const { return FMT == kMX ? v[i] : v[i] * step[i / 4]; }
-  // x - value, exact in float32 for bf16 x
+  // the value up to its sign
+  __device__ __forceinline__ float magnitude(int i) const { return FMT == kMX ? v[i] : v[i] * step[i / 4]; }
+  // x - value (x the element that was quantized), exact in float32 for bf16 x
   __device__ __forceinline__ float residual(int i, float x) const {
-    return FMT == kMX ? x - v[i] : fmaf(-v[i], step[i / 4], x);
+    return FMT == kMX ? x - v[i] : fmaf(-copysignf(v[i], x), step[i / 4], x);
   }
   __device__ __forceinline__ uint32_t nibbles() const {  // all eight codes as nibbles
     if constexpr (FMT == kMX) return w;
@@ -222,7 +223,7 @@ __device__ __forceinline__ Q8<FMT> quantize8(const float x[8]) {
   float a4[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
-    a4[h] = fmaxf(fmaxf(fabsf(x[4 * h]), fabsf(x[4 * h + 1])), fmaxf(fabsf(x[4 * h + 2]), fabsf(x[4 * h + 3])));
+    a4[h] = fmaxf(fmaxf(fmaxf(fmaxf(fabsf(x[4 * h]), fabsf(x[4 * h + 1])), fabsf(x[4 * h + 2])), fabsf(x[4 * h + 3])), 0.f);  // 0 for NaN alone
   const float a = fmaxf(a4[0], a4[1]);
   if constexpr (FMT == kMX) {
     const int E = mx_exponent(group_max<4>(a));
@@ -773,7 +774,7 @@ __device__ __forceinline__ void residual_frag_tile(
         // the keys its passes decode from these codes (one float32 per value)
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          hist_add_copies(ehist_lds, 256, (__float_as_uint(q.value(i)) >> 23) & 255u, row < m && col0 < d);
+          hist_add_copies(ehist_lds, 256, (__float_as_uint(q.magnitude(i)) >> 23) & 255u, row < m && col0 < d);
       }
     } else {
       store_record8<FMT>(fr, fsr, rec, s, q, tab);

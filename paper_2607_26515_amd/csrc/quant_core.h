@@ -59,8 +59,8 @@ __device__ __forceinline__ Quad quantize_quad(const float x[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float k = hif4_round(x[i], g);
-      q.code[i] = ((__float_as_uint(x[i]) >> 28) & 8u) | (uint32_t)fabsf(k);
-      q.val[i] = k * g.step;
+      q.code[i] = ((__float_as_uint(x[i]) >> 28) & 8u) | (uint32_t)k;
+      q.val[i] = copysignf(k * g.step, x[i]);
     }
   }
   return q;
