@@ -1,8 +1,8 @@
 """Channel selection where its kernels can go wrong: channel counts at the edges of the key
-kernel's 64-channel workgroups, of the top-k's 1024-key slots and of its largest register form
-(20480 keys; more are streamed); row counts at the edges of the 128-row steps and the four steps
-loaded together; and the top-k's ways to its threshold (all tied, thousands tied at the threshold,
-few distinct keys, zero channels below an ordinary range, keys far apart).  Masks equal the
+kernel's 64-channel workgroups, of the top-k's 1024-key slots and of the keys that fit its LDS
+(20480; more are streamed); row counts at the edges of the 128-row steps and the four steps
+loaded together; and keys that are all tied, few and distinct, zero for some blocks or far apart.
+Hundreds to thousands of ties at the threshold are test_gpu_channel_ties.py's.  Masks equal the
 oracle's bit for bit."""
 import numpy as np
 import pytest
