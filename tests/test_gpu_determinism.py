@@ -1,4 +1,5 @@
-"""Run-to-run determinism of every GEMM plan, bit for bit.
+"""Run-to-run determinism of every GEMM plan, bit for bit: the LDS-staged ones (INSTANTIATED) and
+those of the streamed kernel for grids of few output tiles (STREAMED).
 
 The GEMM sums each output in a fixed order (no atomics; K groups and K splits are added in
 group and split order), so two calls with identical inputs must give identical bits.  A
@@ -48,7 +49,7 @@ def _plan_key(P, fmt, M, N, K, split):
     return (fmt, p["tile"], p["kgroups"], p["stages"], p["ksplit"] > 1)
 
 
-# every (format, tile, K groups, stages, K split) that launch_gemm can run
+# every (format, tile, K groups, stages, K split) that launch_gemm can run through LDS stages
 INSTANTIATED = {
     ("mxfp4", "64x64", 2, 4, False), ("mxfp4", "64x64", 4, 4, False), ("mxfp4", "64x64", 4, 2, False),
     ("mxfp4", "64x64", 1, 4, False), ("mxfp4", "128x256", 1, 4, False), ("mxfp4", "128x256", 1, 4, True),
@@ -156,3 +157,49 @@ def test_split_k_from_any_workspace(fmt, wl_name, lin_name, sp):
     torch.cuda.synchronize()
     assert _same_bits(y1, y3), f"dirty workspace: {int((y1 != y3).sum())} outputs differ"
     assert _same_bits(y2, y3), f"reused workspace: {int((y2 != y3).sum())} outputs differ"
+
+
+# every (format, tile, waves, K steps ahead, K split) of the streamed kernel that a plan uses, and
+# forward sizes (m, d, n) that run them
+STREAMED = {
+    ("mxfp4", "32x32", 8, 2, False), ("mxfp4", "32x32", 8, 2, True), ("mxfp4", "32x64", 8, 2, False),
+    ("mxfp4", "32x64", 4, 2, False), ("hif4", "32x32", 8, 1, False), ("hif4", "32x32", 8, 1, True),
+    ("hif4", "32x64", 8, 1, False), ("hif4", "32x96", 8, 1, False), ("hif4", "32x64", 4, 1, False),
+}
+STREAM_CASES = [(16, 2048, 2048), (256, 2048, 2048), (128, 3584, 4608), (8, 2048, 22016), (40, 2048, 22016),
+                (8, 65536, 256), (100, 65536, 100), (255, 11008, 2048)]
+
+
+def test_cases_cover_every_streamed_plan():
+    """CPU: STREAM_CASES run every streamed plan, and these are all that the kernel instantiates."""
+    import os
+    import re
+    import paper_2607_26515_amd as P
+    seen = {_plan_key(P, fmt, m, n, d, True) for fmt in FMTS for m, d, n in STREAM_CASES}
+    assert {k for k in seen if k[1].startswith("32x")} == STREAMED
+    src = open(os.path.join(os.path.dirname(P.__file__), "csrc", "gemm_stream.h")).read()
+    built = re.findall(r"X\((\d), (\d), (\d), (\d)\)", src)
+    assert {(FMTS[int(f)], f"32x{32 * int(tn)}", int(w), int(u)) for f, tn, w, u in built} == {k[:4] for k in STREAMED}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("sp", ["none", "2:4"])
+@pytest.mark.parametrize("m,d,n", STREAM_CASES)
+def test_streamed_twice_same_bits(fmt, sp, m, d, n):
+    """The waves' tiles are added through LDS in wave order, the splits' in split order: two calls,
+    the second from a workspace full of 0xFF bytes, give the same bits."""
+    import torch
+    import paper_2607_26515_amd as P
+    from synth import activations, rng_tree, weights
+    log(f"determinism streamed {fmt} {sp} m={m} d={d} n={n} plan={P.gemm_plan(fmt, m, n, d, True)}")
+    rx, rw = rng_tree(m + d + n, 2)
+    x = dev_bf16(activations(rx, m, d, 0.01, 50.0))
+    wprep = P.prepare_weights(*P.quantize(dev_bf16(weights(rw, n, d)), fmt), fmt)
+    ws = P.workspace(P.OP_LINEAR_FWD_PREPARED, fmt, P.sparsity_code(sp), m, d, n, x.device)
+    ws[0].zero_()
+    y1 = P.linear_fwd_prepared(x, wprep, n, fmt, sp, ws=ws)
+    ws[0].fill_(255)
+    y2 = P.linear_fwd_prepared(x, wprep, n, fmt, sp, ws=ws)
+    torch.cuda.synchronize()
+    assert _same_bits(y1, y2), f"two identical calls differ ({int((y1 != y2).sum())} outputs)"

@@ -60,3 +60,27 @@ def test_streamed_forward(fmt, sp, m, d, n):
     assert_close(got[:, :n][:, cols], want, f"Y {fmt} {sp}")
     assert (got[:, n:] == 7.0).all(), "a store left its row"
     assert np.array_equal(host(yb).view(np.uint16), Q.round_to_bf16(got[:, :n]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("m,d,n", CASES)
+def test_streamed_every_column_tile_and_same_bits(fmt, m, d, n):
+    """Every 29th column, so that each 32-column tile is compared, with the columns' places in a
+    workgroup's 32, 64 or 96 all occurring; and a second call into another Y gives the same bits."""
+    import torch
+    import paper_2607_26515_amd as P
+    d = d if fmt == "mxfp4" else d // 64 * 64
+    log(f"streamed gemm columns {fmt} m={m} d={d} n={n} plan={_plan(P, fmt, m, d, n)}")
+    rx, rw = rng_tree(3 * m + d + n, 2)
+    xb, wb = activations(rx, m, d, 0.01, 50.0), weights(rw, n, d)
+    qc, qs = P.quantize(dev_bf16(wb), fmt)
+    wp = P.prepare_weights(qc, qs, fmt)
+    x = dev_bf16(xb)
+    y = P.linear_fwd_prepared(x, wp, n, fmt, "2:4", y=torch.full((m, n), float("nan"), device="cuda"))
+    y2 = P.linear_fwd_prepared(x, wp, n, fmt, "2:4", y=torch.full((m, n), 7.0, device="cuda"))
+    assert torch.equal(y.view(torch.int32), y2.view(torch.int32)), "two identical calls differ"
+    cols = np.arange((m + d) % 29 % n, n, 29)
+    o = Q.resq_quantize_residual(fmt, "2:4", bf16_bits_to_f32(xb))
+    w = F.dequantize(fmt, *F.quantize(fmt, bf16_bits_to_f32(wb[cols])))
+    assert_close(host(y)[:, cols], (o["xhat"] + o["srhat"]) @ w.T, f"Y {fmt}")
