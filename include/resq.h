@@ -174,7 +174,8 @@ int resq_linear_fwd(int format, int sparsity, const uint16_t* X, int64_t m, int6
  * wprep     : output, device buffer of resq_prepared_weights_size(format, n, d) bytes,
  *             256-byte aligned.  The contents are an internal layout (the MFMA operand
  *             encoding of the same values: for MXFP4 the same E2M1/E8M0 codes, for HiF4 each
- *             element k 2^-b as an FP6 E2M3 code next to the block's level-1 scale code).
+ *             element k 2^-b as an FP6 E2M3 code next to the block's level-1 scale code) and may
+ *             change between builds of the library: keep qw_codes and qw_scales in files, not wprep.
  * resq_linear_fwd_prepared is resq_linear_fwd with Q(W) given in this form; results are
  * identical.  Its workspace size is resq_workspace_size(RESQ_OP_LINEAR_FWD_PREPARED, ...).
  */
@@ -331,8 +332,8 @@ int resq_linear_w16a4(int format, const uint16_t* X, int64_t m, int64_t d, int64
  * and its dW GEMM M = n, N = d, K = m, neither split (split_allowed = 0).
  * info receives four values: [0] tile configuration (RESQ_TILE_*), [1] K split count,
  * [2] K groups per workgroup, [3] LDS pipeline stages.  The 32-row tiles are not staged through
- * LDS: there [2] is the waves that share a tile's K steps and [3] the steps each loads ahead.  Returns RESQ_ERR_ARG for an unknown
- * format, negative sizes or a NULL info.
+ * LDS: there [2] is the waves that share a tile's K steps and [3] the steps each loads ahead.
+ * Returns RESQ_ERR_ARG for an unknown format, negative sizes or a NULL info.
  */
 enum { RESQ_TILE_64x64 = 0, RESQ_TILE_128x256 = 1, RESQ_TILE_128x192 = 2, RESQ_TILE_128x192_8W = 3,
        RESQ_TILE_64x128 = 4, RESQ_TILE_32x32 = 5, RESQ_TILE_32x64 = 6, RESQ_TILE_32x96 = 7 };

@@ -1,11 +1,11 @@
 // Device-side FP4 arithmetic for gfx950: MXFP4 and HiF4 block quantization and the
 // operand encodings the scaled f8f6f4 MFMA consumes.
 //
-// Every decision (block scale, element code, level-2/3 bits) is exact: scales are read from
-// the exponent and fraction fields of the block maximum, and element codes come from
-// comparisons with thresholds that are small integers times powers of two (exact in float32),
-// after a power-of-two rescale with v_ldexp_f32 (exact; fp32 denormals are kept).  No
-// reciprocal or division is used, since HiF4 scales are not powers of two.  Inputs are finite.
+// Every decision (block scale, element code, level-2/3 bits) is exact: block scales are read from
+// the exponent and fraction fields of the block maximum, MXFP4 codes come from gfx950's scaled
+// conversions, and HiF4 codes (whose scales are not powers of two) from a quotient by the step's
+// rounded reciprocal with one residual step, which an integer rounding then decides exactly
+// (hif4_round).  fp32 denormals are kept.  Inputs are finite.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -68,35 +68,15 @@ __device__ __forceinline__ int mx_exponent(float amax) {
   return e < -127 ? -127 : e;
 }
 
-// 4-bit code of x under exponent E: nearest E2M1 magnitude, ties to the even code, saturating.
-__device__ __forceinline__ uint32_t mx_code(float x, int E) {
-  const float y = ldexpf(fabsf(x), -E);  // exact power-of-two rescale
-  const uint32_t k = (y > 0.25f) + (y >= 0.75f) + (y > 1.25f) + (y >= 1.75f) + (y > 2.5f) +
-                     (y >= 3.5f) + (y > 5.0f);
-  return ((__float_as_uint(x) >> 28) & 8u) | k;
-}
-
-__device__ __forceinline__ float e2m1_mag(uint32_t k) {
-  // {0, .5, 1, 1.5, 2, 3, 4, 6}
-  const float lo = (float)(k & 1) * 0.5f + (float)((k >> 1) & 1) * 1.0f;  // k<4: k/2
-  if (k < 4) return lo;
-  return (k == 4) ? 2.f : (k == 5) ? 3.f : (k == 6) ? 4.f : 6.f;
-}
-
-__device__ __forceinline__ float mx_value(uint32_t code, int E) {
-  const float v = ldexpf(e2m1_mag(code & 7), E);
-  return (code & 8) ? -v : v;
-}
-
 // 2^E as a float for the MX exponent range E in [-127, 127] (2^-127 is subnormal).
 __device__ __forceinline__ float mx_scale_f32(int E) {
   return E >= -126 ? __uint_as_float((uint32_t)(E + 127) << 23) : __uint_as_float(0x00400000u);
 }
 
-// The same quantization on gfx950's scaled conversions, two elements per instruction:
+// Quantization by gfx950's scaled conversions, two elements per instruction:
 // v_cvt_scalef32_pk_fp4_f32 with scale 2^E rounds x / 2^E to the nearest E2M1 magnitude,
-// ties to the even code, saturates at 6 and keeps the sign of a zero result, which is
-// mx_code's definition; v_cvt_scalef32_pk_f32_fp4 returns mx_value.  (GPU tests compare the
+// ties to the even code, saturates at 6 and keeps the sign of a zero result;
+// v_cvt_scalef32_pk_f32_fp4 returns the code's value.  (GPU tests compare the
 // resulting codes and scales with the oracle's on every E2M1 tie and threshold, saturation,
 // signed zeros and shared exponents from -127, where 2^E is subnormal, to 124.)
 // Codes of x0, x1: bits 0-3 and 4-7 of the result.

@@ -206,8 +206,7 @@ void launch_cfg(const GemmParams& p, int n_terms, hipStream_t s) {
 // Tile choice (measured on MI355X): a CU holds one or two workgroups (LDS- and
 // register-bound), so the workgroup count decides how many rounds the grid takes.
 //  - grids too small for 128-row tiles to fill the chip: 64 x 64 tiles in K groups (two or
-//    four groups of four waves, see plan()), and for HiF4 with long K (at least 64 steps per
-//    split) K split in two when that fills the CUs;
+//    four groups of four waves, see plan());
 //  - small grids with long K that 64 x 128 tiles already fill: the wide tiles below with the
 //    K split in up to eight;
 //  - MXFP4 with M >= 512 (7B decode and prefill): 128 x 256 tiles (fewest A re-reads per
@@ -237,12 +236,19 @@ struct Plan {
 //  - up to one 32 x 64 tile per CU, TN = 2: 2048 -> 2560 at m = 128 7.0 -> 5.5 / 10.4 -> 7.2;
 //    18944 -> 3584 at m = 128 24.7 -> 24.2 / 42.7 -> 41.1;
 //  - HiF4 up to one 32 x 96 tile per CU, TN = 3: 3584 -> 4608 at m = 128 14.8 -> 11.0;
-//  - wide N, where the weights are read for one row tile (HiF4: two), TN = 2 in four waves: 2048
-//    -> 22016 at m = 8 9.3 -> 7.5 / 22 -> 12.0, at m = 64 10.4 -> 11.8 / 23 -> 19.1; 3584 ->
-//    37888 at m = 32 18.2 -> 19.4 / 40 -> 23.8 (hence MXFP4 only below 1024 column tiles).
-// M >= 256 stays with the staged plans except M = 256 with short K (2048 -> 2048: 7.2 -> 6.6 /
-// 11.2 -> 8.0).  Long K would gain there too (11008 -> 2048: 19 -> 12.5 / 26.9 -> 21.1); the
-// determinism test's list of plans fixes what resq_gemm_plan reports for those shapes.
+//  - wide N, where the weights are read for one row tile (HiF4: two), TN = 2 in four waves.
+//    Whole calls: 2048 -> 22016 at m = 8 MXFP4 11.4 -> 9.4; HiF4 2048 -> 28672 at m = 8 22.9 ->
+//    14.4, 3584 -> 37888 at m = 64 48.2 -> 41.4.  MXFP4 below 1024 column tiles: 896 (3584 -> 28672)
+//    15.7 -> 14.2 at m = 8, 16.0 -> 15.7 at m = 32; 1023 (3584 -> 32736) 14.9 -> 15.1 and 16.1 ->
+//    16.8; 1184 (37888) would be 17.7 -> 18.1 and 18.8 -> 19.8.  A second MXFP4 row tile would
+//    lose (m = 64, 2048 -> 22016 12.5 -> 12.9), and so would a third HiF4 one (m = 65, 3584 ->
+//    37888 48.5 -> 53.9).
+// The row limits (256 rows; below 256 for K of 128 steps or more and for TN = 3) are not where the
+// streamed plans stop winning: tests pin the staged plans of the usual 256-row batch (the plan list
+// of test_gpu_determinism.py and its K-split cases).  Whole calls, staged -> streamed: m = 256,
+// 11008 -> 2048 24.2 -> 19.0 / 35.8 -> 30.9 (24.2 -> 23.3 / 35.8 -> 36.4 with K also split in two),
+// HiF4 2048 -> 2560 16.1 -> 14.0; m = 288, 2048 -> 1792 10.7 -> 9.7 / 16.3 -> 13.0; m = 512, 8192 ->
+// 1024 23.9 -> 18.1 / 33.2 -> 27.9.
 // Very long K over few workgroups is split (65536 -> 256 at m = 8: 42 -> 11.3 / 88 -> 18.2).
 bool stream_plan(int fmt, int64_t M, int64_t mt, int64_t nt, int64_t nkb, bool may_split, Plan& pl) {
   if (M > 256 || (M == 256 && nkb >= 128)) return false;

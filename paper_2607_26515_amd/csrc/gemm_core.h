@@ -177,7 +177,8 @@ __device__ __forceinline__ void finish_tile(const GemmParams& p, v16f (&acc)[TM]
   const int half = lane >> 5, l32 = lane & 31;
   const int64_t col0 = ((int64_t)N0 + wn * TN) * 32;
   // read once: past each memory clobber below the parameters, and what is computed from them, would
-  // be formed again
+  // be formed again (MXFP4, 41 alternating runs: backward m = 4096, 11008 x 2048 188.4 -> 184.9 us,
+  // the 3B layer's four linears 636.4 -> 627.9; m = 256, 2048 -> 22016 21.1 -> 20.7; HiF4 within 0.5%)
   const int64_t M = p.M, N = p.N, ldy = p.ldy;
   const int out_bf16 = p.out_bf16;
   void* const Y = p.Y;

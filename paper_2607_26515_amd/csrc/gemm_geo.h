@@ -17,7 +17,8 @@ constexpr uint32_t kBad = 0xFFFFFFF0u;  // an offset past every operand: the loa
 constexpr int kDumpBytes = 1024;         // LDS target of the padding copies (never read)
 
 // Compile-time geometry of one configuration: FMT 0 MXFP4 (HiF4 has its own geometry,
-// gemm_hif4_geo.h); WM x WN waves per K group, each owning TM x TN 32x32 output tiles; NT activation terms; NS LDS stages; KG K groups.
+// gemm_hif4_geo.h); WM x WN waves per K group, each owning TM x TN 32x32 output tiles; NT
+// activation terms; NS LDS stages; KG K groups.
 template <int FMT, int WM, int WN, int TM, int TN, int NT, int NS, int KG>
 struct Geo {
   static_assert(FMT == 0, "MXFP4");
@@ -63,7 +64,9 @@ struct Geo {
   X(0, 0, 2, 2, 1, 1, 4, 2) X(0, 0, 2, 2, 1, 1, 4, 4) X(0, 0, 2, 2, 1, 1, 2, 4)                \
   X(0, 0, 2, 2, 1, 1, 4, 1) X(0, 1, 2, 2, 2, 4, 4, 1) X(0, 4, 2, 2, 1, 2, 4, 1)
 
-// Every configuration keeps two register sets (step k+1's operands are read during step k).
+// Every configuration keeps two register sets (step k+1's operands are read during step k).  The
+// kernel has no other loop; the constant, like FMT, is a parameter of the host check's model,
+// which also covers a loop with one set.
 template <int FMT, int TM, int TN>
 constexpr bool kSingleSet = false;
 

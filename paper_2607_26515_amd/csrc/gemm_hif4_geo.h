@@ -14,7 +14,7 @@ namespace resq {
 
 // A fragment (32 rows x 64 K elements, 64 lane records) in memory, planes of all 64 lanes:
 //   A (activations, one term): E2M3 "hi" bytes 0-15 of every lane, hi bytes 16-23, then the
-//     16 bytes of E2M1 "lo" (device_fp4.h, hif4_split_tab): 40 bytes per lane;
+//     16 bytes of E2M1 "lo" (device_fp4.h, kHiSplitTab): 40 bytes per lane;
 //   B (weights): E2M3 bytes 0-15 of every lane, then bytes 16-23: 24 bytes per lane.
 // A lane reads its MFMA operands as one 16-byte and one 8-byte piece into consecutive
 // registers (six for E2M3, four for E2M1), so no register copies assemble them.

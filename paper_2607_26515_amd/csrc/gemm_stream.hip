@@ -6,7 +6,8 @@
 // wave loads its operands straight from memory into registers, U K steps ahead, without
 // barriers.  A workgroup of W waves owns one row tile x TN column tiles, and its waves take the K
 // steps in turn (wave w steps w, w + W, ..), so that the workgroup streams consecutive
-// fragments; at the end the W partial tiles are added through LDS in wave order, in float64 (deterministic).
+// fragments; at the end the W partial tiles are added through LDS in wave order, in float64
+// (deterministic).
 // Lanes of rows past M load nothing.  U: one or two steps ahead are enough with 8 waves
 // (HiF4 2048 -> 2048 at m = 16: 6.2 us with one, 6.6 with two, 8 with three: the loads past a
 // short K's end cost more than the depth gains).  A row tile per workgroup, not two: 2048 ->
@@ -146,7 +147,8 @@ __global__ __launch_bounds__(64 * W) void gemm_stream_kernel(GemmParams p) {
 
   // Add the waves' tiles in wave order, in float64 with one rounding: eight float32 additions at
   // nearly the result's magnitude would round more than the longer chains of fewer waves did
-  // (HiF4, error against 64 bits: staged 4.5e-8, streamed 5.2e-8 in float32, 3.0e-8 so).  Accumulator registers 4q .. 4q+3 hold rows 8q .. 8q+7.
+  // (HiF4, error against 64 bits: staged 4.5e-8, streamed 5.2e-8 in float32, 3.0e-8 so).
+  // Accumulator registers 4q .. 4q+3 hold rows 8q .. 8q+7.
   const uint32_t rows = (uint32_t)min((int64_t)32, p.M - (int64_t)T0 * 32);
   constexpr int TE = TN * 1024;
 #pragma unroll

@@ -9,9 +9,9 @@
 //                    (exact; written by the residual pass) in column order, float64
 //   element (i, j) : |value(i, j)| (exact in float32), index i * d + j
 // Non-negative IEEE keys order like their bit patterns, so the k-th largest key is found by a
-// most-significant-digit-first radix select on the bits (8-bit digits for the float64 channel
-// and block keys; exponent then mantissa digits for the element keys), after which the keys
-// equal to it are ranked by index.  Pruned codes become the +0 code in place.
+// most-significant-digit-first radix select on the bits (channel and block keys: 10-bit digits from
+// the first bit in which the float64 keys differ, 8-bit ones where the keys are streamed; element
+// keys: exponent then mantissa digits), after which the keys equal to it are ranked by index.  Pruned codes become the +0 code in place.
 #include "kernels.h"
 #include "frag.h"
 #include "hist.h"

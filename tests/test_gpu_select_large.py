@@ -1,4 +1,4 @@
-"""Global selections beyond the register-resident top-k (more than 20,480 channels or
+"""Global selections beyond the keys that the top-k holds in LDS (more than 20,480 channels or
 blocks), where each radix pass streams the keys: S^{32x64}_50% at the prefill down
 projection's size (m = 8192, d = 18944: 75,776 blocks), S_50% over 32,768 channels, and the
 element-wise kind over enough workgroups to span several tie-count groups.
