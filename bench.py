@@ -2,10 +2,12 @@
 """Throughput of the Rollout-ResQ FP4 linear layer on one MI355X.
 
 A default run prints one JSON line whose headline (value, roofline, cpu_baseline) is the
-default workload below, and which carries, under one key each (EXTRA_ENTRIES), the same
-measurement of the rest of the metric taken in the same process: MXFP4 on the same block,
-the Qwen2.5-7B block at m = 512 with the channel, 32x64-block and element-wise residuals in
-both formats, the m = 8192 prefill linears and the m = 8192 training backward in both formats.
+default workload below, and which carries, under one key each (EXTRA_ENTRIES) as [ms per step,
+value, roofline fraction], the same measurement of the rest of the metric taken in the same
+process: MXFP4 on the same block, the Qwen2.5-7B block at m = 512 with the channel, 32x64-block
+and element-wise residuals in both formats, the m = 8192 prefill linears and the m = 8192
+training backward in both formats.  The line is kept short (compact_line), so that the tail of a
+log holds it whole; every entry's whole record goes to stderr as a JSON line of its own.
 
 A step is one rollout forward of every linear projection of one transformer block (the hot
 path of Eq. 4): for each linear, quantize the bf16 activations, form and quantize the
@@ -40,6 +42,7 @@ FP4_PEAK_TFLOPS = 10100.0      # MI355X dense MXFP4 / MXFP6 MFMA
 LLC_BYTES = 256 << 20          # MI355X last-level (Infinity) cache
 
 BYTES_PER_ELEM = {"hif4": 36 / 64, "mxfp4": 17 / 32}  # codes + block scales
+MAX_LINE = 1900                # characters of the printed JSON line
 METRIC = "ResQ FP4 linear TFLOP/s + % roofline (HBM GB/s decode, MFMA FP4 prefill)"
 DEFAULT_WORKLOAD = "qwen3b_layer_m256"
 # Entries measured after the headline in a default run: (key, workload, format, sparsity)
@@ -88,7 +91,7 @@ def executed_flops(m, d, n, sp):
 
 def issued_mfma_flops(m, d, n, fmt, sp):
     """MFMA work the GEMM issues at the FP4/FP6 rate: the executed work, twice for HiF4
-    (each HiF4 term runs as two E2M3 operands, hi and lo, so its level-1 scale fits)."""
+    (each HiF4 term runs as an E2M3 and an E2M1 operand, hi and lo, so its level-1 scale fits)."""
     return executed_flops(m, d, n, sp) * (2 if fmt == "hif4" else 1)
 
 
@@ -168,17 +171,20 @@ def cpu_baseline(wl, fmt, sp, n_sample, n_rows, min_seconds):
         if time.perf_counter() - t0 >= min_seconds:
             break
     dt = time.perf_counter() - t0
-    what_ = ("dY, X and W restricted to" if wl.backward else "X restricted to")
     return {
-        "value": flops / dt / 1e12,
+        "value": round(flops / dt / 1e12, 6),
         "unit": "TFLOP/s",
         "cores": int(blas_threads or cores),
         "kind": "oracle",
-        "sample": (f"{wl.name}: {what_} the first {rows} rows and the first {n_sample} output "
-                   f"features of every linear, {reps} repetition(s), {dt:.1f} s"
-                   f"{'' if wl.backward else '; Q(W) untimed'}; numpy fp64 (quantizers "
-                   f"single-threaded, matmul on {blas_threads or '?'} BLAS threads of {cores} cores)"),
+        "sample": cpu_sample_text(wl.name, rows, n_sample, reps, dt, blas_threads or "?", wl.backward),
     }
+
+
+def cpu_sample_text(name, rows, features, reps, seconds, threads, backward=False):
+    """What the oracle's time was measured on."""
+    return (f"{name}: {'dY, X and W' if backward else 'X'} restricted to {rows} rows and {features} output features per "
+            f"linear, {reps} repetition(s), {seconds:.1f} s{'' if backward else ', Q(W) untimed'}; numpy fp64, matmul on "
+            f"{threads} threads")
 
 
 def bench_diagnostics(args, P, torch, np, wl, fmt, dev, sptr):
@@ -726,6 +732,7 @@ def main() -> int:
         "data": "synthetic",
     }
     out.update(result)
+    print(json.dumps(out), file=sys.stderr, flush=True)
     if not args.no_extra and args.workload == DEFAULT_WORKLOAD:
         # the rest of the metric, measured in the same process: the other format on the
         # same workload, the m = 512 block, prefill and the training backward
@@ -739,11 +746,30 @@ def main() -> int:
             else:
                 e = measure(args, P, torch, np, WORKLOADS[wl_name], f, sp, "f32", dev, sptr, run_stream,
                             args.extra_cpu_seconds)
-            out[name] = e
-            print(f"bench.py: {name}: {e['ms_per_step']} ms/step, roofline frac "
-                  f"{e['roofline']['frac']}", file=sys.stderr, flush=True)
-    print(json.dumps(out), flush=True)
+            out[name] = [round(e["ms_per_step"], 4), round(e["value"], 1), e["roofline"]["frac"]]
+            print(json.dumps({name: e}), file=sys.stderr, flush=True)
+    print(compact_line(out), flush=True)
     return 0
+
+
+def compact_line(out):
+    """The JSON line of `out` without the detail that stderr has, below MAX_LINE characters."""
+    out = dict(out)
+    for k in ("step_hbm", "per_linear_us", "kernel_ms_per_step"):
+        out.pop(k, None)
+    out["roofline"] = {k: v for k, v in out["roofline"].items()
+                       if k not in ("flops_counted", "hbm_gbs", "alg_tflops", "mfma_issued_tflops", "exec_flops_per_launch")}
+    return json.dumps(out, separators=(",", ":"))
+
+
+def gemm_kernels(P, wl, fmt):
+    """Names of the GEMM kernels that the workload's plans launch."""
+    if wl.backward:
+        plans = [P.gemm_plan(fmt, *mnk, False) for l in wl.linears for mnk in ((wl.m, l.d, l.n), (l.n, l.d, wl.m))]
+    else:
+        plans = [P.gemm_plan(fmt, wl.m, l.n, l.d, True) for l in wl.linears]
+    staged = "gemm_hif4_kernel" if fmt == "hif4" else "gemm_kernel"
+    return " + ".join(sorted({"gemm_stream_kernel" if p["tile"].startswith("32x") else staged for p in plans}))
 
 
 def measure(args, P, torch, np, wl, fmt, sparsity, out_t, dev, sptr, run_stream, cpu_seconds,
@@ -839,7 +865,7 @@ def measure(args, P, torch, np, wl, fmt, sparsity, out_t, dev, sptr, run_stream,
         "unit": "TFLOP/s" if mfma_bound else "GB/s",
         "frac": round(exec_tflops / FP4_PEAK_TFLOPS if mfma_bound else hbm_gbs / HBM_PEAK_GBS, 4),
         "traffic": gemm_traffic(wl.name, fmt, sp, out_t),
-        "kernel": f"gemm_kernel ({n_launch} launches per step)",
+        "kernel": f"{gemm_kernels(P, wl, fmt)} ({n_launch} launches per step)",
         "alg_bytes_per_launch": round(gbytes / n_launch),
         "exec_flops_per_launch": round(gexec / n_launch),
         "flops_counted": "executed: 2mnd per term, the residual as a dense FP4 operand (Sec. 5.4 on gfx950)",

@@ -86,3 +86,36 @@ def test_extra_entries_cover_the_metric():
 
 def test_traffic_lookup_misses_give_none():
     assert bench.gemm_traffic("no_such_workload", "hif4", "2:4") is None
+
+
+def test_default_line_stays_short_and_whole():
+    """The default run's JSON line, with figures of the longest forms they take, fits MAX_LINE and
+    carries the headline, its roofline and CPU baseline, and one entry per extra workload."""
+    import json
+    from synth import WORKLOADS
+    out = {"metric": bench.METRIC, "value": 1234.567, "unit": "TFLOP/s", "n_gpus": 1, "steps": 20, "warmup": 5,
+           "ms_per_step": 0.12345, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "fp4",
+           "data": "synthetic",
+           "config": {"workload": "qwen3b_layer_m256", "format": "hif4", "sparsity": "2:4", "pass": "forward",
+                      "output": "float32", "m": 256,
+                      "linears": {l.name: [l.d, l.n] for l in WORKLOADS[bench.DEFAULT_WORKLOAD].linears},
+                      "copies_rotated": 9},
+           "step_hbm": {"alg_bytes": 123456789, "achieved_gbs": 1234.5, "frac": 0.1234},
+           "kernel_ms_per_step": {"residual": 0.01234, "pack_hif4": 0.0, "select": 0.0, "gemm": 0.12345},
+           "per_linear_us": {"qkv": {"residual": 12.34, "pack_hif4": 0.0, "select": 0.0, "gemm": 12.34}},
+           "roofline": {"bound": "hbm", "achieved": 1234.5, "peak": 8000.0, "unit": "GB/s", "frac": 0.1234,
+                        "traffic": 123456789, "kernel": "gemm_hif4_kernel + gemm_stream_kernel (4 launches per step)",
+                        "alg_bytes_per_launch": 123456789, "exec_flops_per_launch": 123456789012, "flops_counted": "x" * 90,
+                        "avg_launch_us": 123.45, "hbm_gbs": 1234.5, "exec_tflops": 1234.5, "exec_frac": 0.1234,
+                        "alg_tflops": 1234.5, "mfma_issued_tflops": 1234.5},
+           "cpu_baseline": {"value": 0.01234, "unit": "TFLOP/s", "cores": 16, "kind": "oracle",
+                            "sample": bench.cpu_sample_text("qwen3b_layer_m256", 256, 1024, 11, 10.2, 16)}}
+    for name, *_ in bench.EXTRA_ENTRIES:
+        out[name] = [12.3457, 12345.7, 0.1234]
+    line = bench.compact_line(out)
+    assert len(line) <= bench.MAX_LINE, len(line)
+    got = json.loads(line)
+    assert {"metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline"} <= set(got)
+    assert {n for n, *_ in bench.EXTRA_ENTRIES} <= set(got)
+    assert {"bound", "achieved", "peak", "unit", "frac", "kernel"} <= set(got["roofline"])
