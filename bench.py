@@ -42,6 +42,8 @@ FP4_PEAK_TFLOPS = 10100.0      # MI355X dense MXFP4 / MXFP6 MFMA
 LLC_BYTES = 256 << 20          # MI355X last-level (Infinity) cache
 
 BYTES_PER_ELEM = {"hif4": 36 / 64, "mxfp4": 17 / 32}  # codes + block scales
+# the GEMM kernels' sources, hashed beside their committed counter summary
+GEMM_SOURCES = ("gemm.hip", "gemm_core.h", "gemm_geo.h", "gemm_hif4.hip", "gemm_hif4_geo.h", "gemm_stream.hip")
 MAX_LINE = 1900                # characters of the printed JSON line
 METRIC = "ResQ FP4 linear TFLOP/s + % roofline (HBM GB/s decode, MFMA FP4 prefill)"
 DEFAULT_WORKLOAD = "qwen3b_layer_m256"
@@ -108,13 +110,13 @@ def gemm_bytes(m, d, n, fmt, sp, y_bytes=4):
 
 def gemm_traffic(workload, fmt, sp, out="f32"):
     """HBM bytes per GEMM launch from the committed rocprofv3 counter summary, or None when
-    the summary does not cover this workload or the GEMM source (gemm.hip and gemm_geo.h)
-    changed since it was taken."""
+    the summary does not cover this workload or the GEMM sources (GEMM_SOURCES) changed since
+    it was taken."""
     import hashlib
     try:
         rec = json.load(open(os.path.join(ROOT, "profiles", "gemm_traffic.json")))
         h = hashlib.sha256()
-        for f in ("gemm.hip", "gemm_geo.h"):  # the GEMM kernel's sources
+        for f in GEMM_SOURCES:
             h.update(open(os.path.join(ROOT, "paper_2607_26515_amd", "csrc", f), "rb").read())
     except OSError:
         return None
