@@ -70,16 +70,15 @@ def test_row_kernel_edges(fmt, rows, cols):
     assert torch.equal(buf[2:].reshape(rows, cols // 2), want)
 
 
-@pytest.mark.parametrize("fmt", ["mxfp4", "hif4"])
-@pytest.mark.parametrize("cols,step", [(32, 32), (64, 32), (96, 16), (128, 16), (192, 8), (256, 8), (320, 4),
-                                       (1024, 2), (1088, 1)])
+LANES = [(32, 32), (64, 32), (96, 16), (128, 16), (192, 8), (256, 8), (320, 4), (1024, 2), (1088, 1)]
+
+
+@pytest.mark.parametrize("fmt,cols,step", [(f, c, s) for f in ("mxfp4", "hif4") for c, s in LANES if f == "mxfp4" or c % 64 == 0])
 def test_row_kernel_lane_counts(fmt, cols, step):
     """Every number of lanes along a row (8 .. 256, widths that fill them and that do not) with row
     counts around the rows of a workgroup (`step`), one workgroup and several."""
     import paper_2607_26515_amd as P
     from synth import bf16_bits_to_f32
-    if fmt == "hif4" and cols % 64:
-        pytest.skip("HiF4 blocks are 64 wide")
     for rows in sorted({1, step - 1, step, step + 1, 5 * step + 1} - {0}):
         log(f"quant rows lanes {fmt} {rows}x{cols}")
         xb = activations(rng_tree(1000 * rows + cols, 1)[0], rows, cols, 0.01, 50.0)
